@@ -42,7 +42,8 @@ KID = {"slp": 0, "dlp": 1}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "far_traffic_icosphere20480.json")
 
 
-TRAFFIC_SOURCES = ["paper_2312_11219_amd/csrc/far_aca.hip", "paper_2312_11219_amd/csrc/device_util.h",
+TRAFFIC_SOURCES = ["paper_2312_11219_amd/csrc/far_aca.hip", "paper_2312_11219_amd/csrc/far_aca_reg.hip",
+                   "paper_2312_11219_amd/csrc/device_util.h",
                    "paper_2312_11219_amd/csrc/entries_dev.h", "paper_2312_11219_amd/csrc/fastmath_dev.h",
                    "paper_2312_11219_amd/csrc/galerkin_dev.h", "paper_2312_11219_amd/csrc/kernels.h",
                    "paper_2312_11219_amd/csrc/internal.h",

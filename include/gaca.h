@@ -106,8 +106,8 @@ typedef struct {
                                  of the problem's last build of the operator); blocks enter the
                                  batches largest (m n) first; the result does not depend on the
                                  batches */
-    int32_t threads_small;    /* face-ACA workgroup size for faces with m n <= 1024: 128
-                                 (default) or 64 (one wave per face) */
+    int32_t threads_small;    /* 128 (default) or 64; without effect since the small faces are held
+                                 in registers with a workgroup chosen by their size */
     int32_t threads_large;    /* face-ACA workgroup size for the large faces (256, 512 or
                                  1024; default 0: chosen by the autotuner if autotune_cache is
                                  set, else 512) */
@@ -181,12 +181,10 @@ typedef struct {
                                      read once + the new face written (m n (l + 1) elements);
                                      expand = U, W read + H_l written + the previous faces read
                                      for the Gram row; aca and tail 0 (not modelled) */
-    /* aca phase by launch class (device time of the class's launches on its stream): 0 m n <= 1024 and sides <= 64 (registers, 128 or 64 threads),
-     * 1 m n <= 2304 and sides <= 96 (registers, 256 threads) together with the faces whose
-     * sides are in (128, 256] when threads_large is above 256 (R in HBM, 256 threads, two
-     * faces per CU), 2 m n <= 4096 and sides <= 128 (registers, 512 threads) together
-     * with the larger faces whose sides are <= 128 (R in HBM, 256 threads), 3 the other
-     * faces with a side above 128 (R in HBM, 512 threads by default) */
+    /* aca phase by launch class (device time of the class's launches on its stream): faces held
+     * in registers with sides up to 32 (0), 33 to 96 (1), above 96 (2: up to 160 in FP64, 192
+     * mixed; together with the faces in HBM whose sides are <= 256 when threads_large is above
+     * 256: 256 threads, two faces per CU); 3 the other faces (R in HBM, 512 threads by default) */
     double ms_far_by_kind[4];
     int32_t launches_by_kind[4];
     double far_flops_by_kind[4];  /* algorithmic flops of the class's face-ACA launches */

@@ -15,9 +15,9 @@
 //
 // The face phase evaluates every entry of every active face in parallel (the kernel
 // evaluations are most of the arithmetic); only the ACA of one face is sequential and runs
-// one workgroup per block.  Small faces (kinds 0/1) stay in LDS through the ACA, which
-// updates R and S = sum_q u_q w_q^T in place and so also produces H_l = S, its pivot and its
-// Gram row; larger faces keep R in HBM and are expanded by the tiled expand phase.
+// one workgroup per block.  Faces with sides up to 160 (mixed 192) are held in registers
+// through it (far_aca_reg.hip), larger ones keep R in HBM; above sides of 64 H_l is formed by
+// the tiled expand phase.
 //
 // Mixed precision: faces, residuals and face factors are FP32 (float2) and every face is
 // kept divided by the block scale c_k = exp(-s_k d0) (d0 = distance of the cluster
@@ -462,167 +462,6 @@ __device__ void zero_rows_split(const FT *R, const FT *Uh, const FT *Wh, const F
 }
 
 // ---------------------------------------------------------------------------------------
-// ACA phase, small faces: R and S = sum_q u_q w_q^T in registers, E = MNMAX / NT entries
-// per thread (entry idx = tid + NT t), updated in place by the rank-1 steps; only the current
-// row, column and w live in LDS, so several faces share a CU.  Also stores H_l = S over R and
-// finds its max, norm and pivot (the Gram row against the previous faces follows in
-// far_gram_small_kernel).
-template <int NT, bool MIXED, int MNMAX, int SIDE>
-__global__ void __launch_bounds__(NT, (NT == 256 && MNMAX == 2304) ? 3 : 1)
-    far_aca_small_kernel(AcaParams P, FarBatchDev bd, const FarActive *act) {
-    using FT = face_t<MIXED>;
-    constexpr int E = MNMAX / NT;
-    static_assert(E * NT == MNMAX, "MNMAX must be a multiple of NT");
-    const FarActive A = act[blockIdx.x];
-    const int b = A.b;
-    const FarBlockDev B = bd.blk[b];
-    const int m = B.m, n = B.n, mn = m * n;
-    const int tid = threadIdx.x;
-    const double zero_tol = bd.st[b].zero_tol, ref2 = bd.st[b].ref2;
-    FT *R = reinterpret_cast<FT *>(bd.hpool) + A.hslot;
-    FT *Ub = reinterpret_cast<FT *>(bd.uw) + B.uw_off;
-    FT *Wb = Ub + (int64_t)B.rho_max * m;
-
-    const int64_t t_start = wall_clock64();
-    __shared__ FT rowv[SIDE];
-    __shared__ FT ucol[SIDE];
-    __shared__ FT wrow[SIDE];
-    __shared__ unsigned char used_row[SIDE];
-    __shared__ double redbuf[8 * (NT / 64) + 4];
-    Red<NT> red{redbuf};
-    const double tie2 = (1.0 - P.tie) * (1.0 - P.tie);
-
-    FT rr[E], ss[E];
-    int ri[E];   // row of entry t; m for entries beyond the face
-#pragma unroll
-    for (int t = 0; t < E; ++t) {
-        const int idx = tid + NT * t;
-        ri[t] = idx < mn ? idx / n : m;
-        rr[t] = idx < mn ? R[idx] : czero<FT>();
-        ss[t] = czero<FT>();
-    }
-    for (int r = tid; r < m; r += NT) used_row[r] = 0;
-    int q = 0, i = 0, nused = 0;
-    double s2 = 0.0;
-    while (true) {
-        // row i of the residual -> LDS (its owners write it)
-#pragma unroll
-        for (int t = 0; t < E; ++t)
-            if (ri[t] == i) rowv[tid + NT * t - i * n] = rr[t];
-        __syncthreads();
-        double mx = 0.0;
-        for (int j = tid; j < n; j += NT) mx = fmax(mx, cabs2(rowv[j]));
-        mx = red.max(mx);
-        if (tid == 0) used_row[i] = 1;
-        ++nused;
-        if (sqrt(mx) <= zero_tol) {
-            // A zero row: the ACA goes on with the unused rows in index order, and every one
-            // below the first with a nonzero residual entry is zero as well; find that row in
-            // one pass over the register-held residual and mark the zero ones used.
-            __syncthreads();
-            int cand = m;
-#pragma unroll
-            for (int t = 0; t < E; ++t)
-                if (ri[t] < m && !used_row[ri[t]] && sqrt(cabs2(rr[t])) > zero_tol) cand = min(cand, ri[t]);
-            cand = red.imin(cand);
-            double cnt = 0.0;
-            for (int r = tid; r < cand; r += NT)
-                if (!used_row[r]) cnt += 1.0;
-            cnt = red.sum(cnt);
-            for (int r = tid; r < cand; r += NT) used_row[r] = 1;
-            nused += (int)cnt;
-            if (cand >= m) break;
-            i = cand;
-            continue;
-        }
-        const double thr = tie2 * mx;
-        int jc = n;
-        for (int j = tid; j < n; j += NT)
-            if (cabs2(rowv[j]) >= thr) {
-                jc = j;
-                break;
-            }
-        const int jp = min(red.imin(jc), n - 1);   // in range even for NaN rows
-        const FT piv = rowv[jp];
-        double nw2 = 0.0, nu2 = 0.0;
-        for (int j = tid; j < n; j += NT) {
-            const FT w = cdiv(rowv[j], piv);
-            wrow[j] = w;
-            Wb[(int64_t)q * n + j] = w;
-            nw2 += cabs2(w);
-        }
-        // column jp of the residual (its owners write it)
-#pragma unroll
-        for (int t = 0; t < E; ++t)
-            if (ri[t] < m && tid + NT * t - ri[t] * n == jp) {
-                const FT u = rr[t];
-                ucol[ri[t]] = u;
-                Ub[(int64_t)q * m + ri[t]] = u;
-                nu2 += cabs2(u);
-            }
-        __syncthreads();
-        double sp = 0.0;
-#pragma unroll
-        for (int t = 0; t < E; ++t)
-            if (ri[t] < m) {
-                const FT tt = cmul(ucol[ri[t]], wrow[tid + NT * t - ri[t] * n]);
-                rr[t] = csub(rr[t], tt);
-                ss[t] = cadd(ss[t], tt);
-                sp += cabs2(ss[t]);
-            }
-        // the maximum of |u_q|^2 over the unused rows (for the next-row pick) shares the
-        // reduction round of the norms
-        double mxu = -1.0;
-        for (int r = tid; r < m; r += NT)
-            if (!used_row[r]) mxu = fmax(mxu, cabs2(ucol[r]));
-        red.sum3max(nu2, nw2, sp, mxu);
-        s2 = sp;
-        ++q;
-        if (sqrt(nu2 * nw2) <= P.eps_aca * sqrt(ref2 + s2) || nused >= m || q >= B.rho_max)
-            break;
-        // next row: the lowest unused row with |u_q|^2 at the tie threshold of that maximum
-        // (the first unused row if none compares)
-        const double thu = tie2 * mxu;
-        int c = 0x7fffffff;
-        for (int r = tid; r < m; r += NT)
-            if (!used_row[r] && cabs2(ucol[r]) >= thu) {
-                c = r;
-                break;
-            }
-        c = red.imin(c);
-        if (c >= m) c = first_unused<NT>(used_row, m, red);
-        i = min(c, m - 1);
-    }
-    const int rho = q;
-    int pidx = 0;
-    double mxh = 0.0, h2 = 0.0;
-    if (rho > 0) {
-#pragma unroll
-        for (int t = 0; t < E; ++t)
-            if (ri[t] < m) {
-                R[tid + NT * t] = ss[t];
-                const double a2 = cabs2(ss[t]);
-                mxh = fmax(mxh, a2);
-                h2 += a2;
-            }
-        red.maxsum(mxh, h2);
-        const double thh = tie2 * mxh;
-        int pc = 0x7fffffff;
-#pragma unroll
-        for (int t = E - 1; t >= 0; --t)   // lowest own index at the threshold
-            if (ri[t] < m && cabs2(ss[t]) >= thh) pc = tid + NT * t;
-        pidx = min(red.imin(pc), mn - 1);
-    }
-    if (tid == 0) {
-        FarStateDev *S = bd.st + b;
-        S->rho = rho;
-        S->pidx = pidx;
-        S->mxh = mxh;
-        S->h2 = h2;
-        S->aca_ticks += wall_clock64() - t_start;
-    }
-}
-
 // ACA phase, large faces: R in HBM; the factor history u_q', w_q' in LDS for the first qL
 // steps (as many as fit) and in HBM beyond, so the row / column corrections and the cross
 // terms of the stopping norm mostly read LDS.  Row and column corrections are split over
@@ -1443,7 +1282,7 @@ __global__ void __launch_bounds__(NT)
 }
 
 // ---------------------------------------------------------------------------------------
-// Expand phase (kind 2): one 32 x 32 tile of H_l = U W^T per wave, written over R, with the
+// Expand phase: one 32 x 32 tile of H_l = U W^T per wave, written over R, with the
 // tile's max |H|^2, sum |H|^2 and Gram partials <H_l, H_p>.  Lane (rg, cg) = (lane / 8,
 // lane % 8) owns the sixteen entries (rg + 8 a, cg + 8 e), a, e < 4: each factor step
 // reads four U and four W values from LDS for sixteen complex products, and for each (a, e)
@@ -1555,8 +1394,8 @@ __global__ void __launch_bounds__(64) far_expand_kernel(FarBatchDev bd, const Fa
     }
 }
 
-// Gram row <H_l, H_p> (p < l) of a small face (kinds 0/1, H_l already stored by the ACA
-// phase), one workgroup per face, written as the face's single partial row.
+// Gram row <H_l, H_p> (p < l) of a face whose H_l the ACA phase has stored, one workgroup per
+// face, written as the face's single partial row.
 __global__ void __launch_bounds__(256) far_gram_small_kernel(FarBatchDev bd, const FarActive *act) {
     const FarActive A = act[blockIdx.x];
     const int b = A.b;
@@ -1933,37 +1772,11 @@ static void aca_dispatch(int path, int threads, const AcaParams &P, const FarBat
     else large_dispatch<MX, 0>(threads, P, bd, act, nact, st);
 }
 
-template <bool MX>
-static void aca_small_dispatch(int mnmax, int threads, const AcaParams &P, const FarBatchDev &bd,
-                               const FarActive *act, int nact, hipStream_t st) {
-    if (mnmax <= 576 && threads <= 64)
-        far_aca_small_kernel<64, MX, 576, 64><<<nact, 64, 0, st>>>(P, bd, act);
-    else if (mnmax <= 1024 && threads <= 64)
-        far_aca_small_kernel<64, MX, 1024, 64><<<nact, 64, 0, st>>>(P, bd, act);
-    else if (mnmax <= 1024)
-        far_aca_small_kernel<128, MX, 1024, 64><<<nact, 128, 0, st>>>(P, bd, act);
-    else if (mnmax <= 2304 && threads <= 64)
-        far_aca_small_kernel<64, MX, 2304, 96><<<nact, 64, 0, st>>>(P, bd, act);
-    else if (mnmax <= 2304 && threads <= 128)
-        far_aca_small_kernel<128, MX, 2304, 96><<<nact, 128, 0, st>>>(P, bd, act);
-    else if (mnmax <= 2304)
-        far_aca_small_kernel<256, MX, 2304, 96><<<nact, 256, 0, st>>>(P, bd, act);
-    else
-        far_aca_small_kernel<512, MX, 4096, 128><<<nact, 512, 0, st>>>(P, bd, act);
-}
-
 void launch_far_aca(int path, int threads, const AcaParams &P, const FarBatchDev &bd,
                     const FarActive *act, int nact, hipStream_t st) {
     if (nact <= 0) return;
     if (bd.mixed) aca_dispatch<true>(path, threads, P, bd, act, nact, st);
     else aca_dispatch<false>(path, threads, P, bd, act, nact, st);
-}
-
-void launch_far_aca_small(int mnmax, int threads, const AcaParams &P, const FarBatchDev &bd,
-                          const FarActive *act, int nact, hipStream_t st) {
-    if (nact <= 0) return;
-    if (bd.mixed) aca_small_dispatch<true>(mnmax, threads, P, bd, act, nact, st);
-    else aca_small_dispatch<false>(mnmax, threads, P, bd, act, nact, st);
 }
 
 void launch_far_expand(const FarBatchDev &bd, const FarActive *act, int64_t ntile, hipStream_t st) {

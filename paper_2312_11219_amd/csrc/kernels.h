@@ -78,24 +78,25 @@ void launch_near_galerkin(int tier, const GeoDev &g, const QuadDev &q, const Fre
 // Far field 3D-ACA, run as iterations over all unfinished blocks of a batch; one iteration
 // adds one face (one 3-D cross, or one zero face) to every active block in four phases:
 //   face    residual face R = ENTRY(:, :, k) - sum_p coef_p H_p, all entries in parallel
-//   aca     partial-pivot ACA of R, one workgroup per block (kinds 0-2: R and S in LDS, which
-//           also expand H_l and pick the pivot; kind 3: R in HBM)
-//   expand  kind 3: H_l = U W^T in 32 x 32 tiles with per-tile max, norm and Gram partials;
-//           kinds 0-2: the Gram row of H_l (one partial row per face)
-//   tail    pivot (kind 2), fibre, eq. (norm), stop test, next frequency and coefficients
+//   aca     partial-pivot ACA of R, one workgroup per block (R in registers up to sides of 160,
+//           mixed 192; R in HBM above)
+//   expand  sides above 64: H_l = U W^T in 32 x 32 tiles with per-tile max, norm and Gram
+//           partials; up to 64 the ACA has stored H_l and found its pivot, and only the Gram row
+//           of H_l follows (one partial row per face)
+//   tail    pivot (expanded faces), fibre, eq. (norm), stop test, next frequency and coefficients
 constexpr int kFarChunk = 256;   // face entries per workgroup of the face phase
 constexpr int kFarTile = 32;     // expand tile side
 constexpr int kFarMaxRows = 8192; // rows / columns of a far block
 __host__ __device__ constexpr int far_part_stride(int rcap) { return 2 + 2 * rcap; }
 
-// One active block of an iteration (host-built, sorted kind 3, 2, 1, 0).
+// One active block of an iteration (host-built, expanded faces first).
 struct FarActive {
     int32_t b;          // batch-local block index
-    int32_t ntile;      // expand tiles (kind 3)
+    int32_t ntile;      // expand tiles (0: the ACA stores H_l)
     int64_t hslot;      // face-type element offset of this face's slot in the H pool
     int64_t fgslot;     // double2 offset of this cross's fibre (L) + Gram row (rcap) slot
     int64_t chunk0;     // first face-phase chunk
-    int64_t tile0;      // first expand tile (kind 3) or the face's partial row (kinds 0-2)
+    int64_t tile0;      // first expand tile, or the face's partial row (no tiles)
 };
 
 struct FarCopy {        // one chunk of the factors of an accepted cross -> arena
@@ -133,17 +134,19 @@ void launch_far_map(const FarBatchDev &bd, const FarActive *act, int nact, int n
                     hipStream_t st);
 void launch_far_face(int kernel, const GeoDev &g, const FreqDev &f, const FarBatchDev &bd,
                      const FarActive *act, int64_t nchunk, hipStream_t st);
-// Classes: kind 0 m n <= 1024, sides <= 64; kind 1 m n <= 2304, sides <= 96; kind 2 m n <=
-// 4096 (FP64) or 8192 (mixed), sides <= 128; kind 3 larger.
-// Kind 3 (R in HBM): threads 256, 512 or 1024; path 1: faces with m, n <= threads; 2: m, n
+// Faces in registers (csrc/far_aca_reg.hip): class c takes both sides <= kFarRegSide[c]; the
+// mixed path all classes, FP64 all but the last (a face of 192 x 192 double2 exceeds the
+// registers of a CU).  Classes up to kFarEmitSide store H_l themselves.
+constexpr int kFarRegClasses = 10;
+constexpr int kFarRegSide[kFarRegClasses] = {24, 32, 40, 48, 64, 80, 96, 128, 160, 192};
+constexpr int kFarEmitSide = 64;
+void launch_far_aca_reg(int cls, const AcaParams &P, const FarBatchDev &bd, const FarActive *act,
+                        int nact, hipStream_t st);
+// Larger faces (R in HBM): threads 256, 512 or 1024; path 1: faces with m, n <= threads; 2: m, n
 // <= kFarMultiE * 512 (512 threads); 0: any face.
 constexpr int kFarMultiE = 5;
 void launch_far_aca(int path, int threads, const AcaParams &P, const FarBatchDev &bd,
                     const FarActive *act, int nact, hipStream_t st);
-// Kinds 0-2 (R and S in registers): faces with m n <= mnmax (576, 1024, 2304, or the kind-2
-// bound) and workgroups of `threads` (64: one wave per face, 128, 256; kind 2: 512).
-void launch_far_aca_small(int mnmax, int threads, const AcaParams &P, const FarBatchDev &bd,
-                          const FarActive *act, int nact, hipStream_t st);
 void launch_far_expand(const FarBatchDev &bd, const FarActive *act, int64_t ntile, hipStream_t st);
 // Recompression of the current faces' factors (QR of both, SVD of the core, truncation at
 // eps_aca), faces of rank 2..kRecMaxRank; nslot workgroups with kRecSlot doubles2 each of ws.
@@ -152,7 +155,7 @@ constexpr int64_t kRecSlot = 6 * (int64_t)kRecMaxRank * kRecMaxRank;
 constexpr int kRecSlots = 256;   // concurrent faces (workgroups) of the recompression
 void launch_far_recompress(const AcaParams &P, const FarBatchDev &bd, const FarActive *act,
                            int nact, double2 *ws, int nslot, hipStream_t st);
-// Gram rows of LDS-resident faces (kinds 0-2) into their single partial row (FarActive::tile0)
+// Gram rows of the faces without expand tiles into their single partial row (FarActive::tile0)
 void launch_far_gram_small(const FarBatchDev &bd, const FarActive *act, int nact, hipStream_t st);
 void launch_far_tail(int kernel, const GeoDev &g, const FreqDev &f, const AcaParams &P,
                      const FarBatchDev &bd, const FarActive *act, int nact, int nlarge,

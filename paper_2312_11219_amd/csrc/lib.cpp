@@ -1066,20 +1066,17 @@ gaca_status gaca_problem_blocks(const gaca_problem *p, int64_t *far4, int64_t *n
 
 // ---------------------------------------------------------------------------------------
 // far-field build
-// Launch class of a far block in the aca phase: faces of kinds 0-2 stay in LDS (R and S,
-// up to 128 KB), kind 3 keeps R in HBM.
-// Large faces with both sides at most this run as medium faces (see run_far).
-constexpr int kMediumSide = 128;
-
-// (The mixed build had FP32 faces of up to 8192 entries in registers too: the faces of 4097
-// to 8192 entries run faster on the one-entry-per-thread kernel, as in the FP64 build.)
-static int far_kind(int m, int n) {
-    const int64_t mn = (int64_t)m * n;
-    if (mn <= 1024 && m <= 64 && n <= 64) return 0;
-    if (mn <= 2304 && m <= 96 && n <= 96) return 1;
-    if (mn <= 4096 && m <= 128 && n <= 128) return 2;
-    return 3;
+// Register class of a face in the aca phase (kFarRegSide), or -1 for the faces whose residual
+// stays in HBM: FP64 faces fit a CU's registers up to sides of 160, mixed ones up to 192.
+static int far_reg_class(int m, int n, bool mixed) {
+    const int side = std::max(m, n), ncls = mixed ? kFarRegClasses : kFarRegClasses - 1;
+    for (int c = 0; c < ncls; ++c)
+        if (side <= kFarRegSide[c]) return c;
+    return -1;
 }
+
+// Faces whose H_l the expand phase forms (the ACA of the smaller ones stores it).
+static bool far_expanded(int m, int n) { return std::max(m, n) > kFarEmitSide; }
 
 // Grow buf to at least need bytes keeping its first `used` bytes (stream-ordered copy).
 static void grow_keep(gaca_context *ctx, DevBuf &buf, size_t need, size_t used, hipStream_t st) {
@@ -1273,15 +1270,14 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
     P.pivot_index = p->opt.pivot_estimate != 0;
     const bool recomp = P.recompress != 0;
 
-    // block descriptors, launch classes and memory estimates
+    // block descriptors and memory estimates
     std::vector<FarBlockDev> desc(ntot);
-    std::vector<int> kind(ntot);
     // memory estimate of a block in a batch with rg faces per block (pool slots, fibres and
     // Gram rows, current factors, expand partials, state)
     auto est_of = [&](int64_t gb, double rg) {
         const double m = (double)desc[gb].m, n = (double)desc[gb].n, mn = m * n;
         const double rho_max = std::min(m, n);
-        const double tiles = far_kind((int)m, (int)n) == 3 ? std::ceil(m / 32.0) * std::ceil(n / 32.0) : 1.0;
+        const double tiles = far_expanded((int)m, (int)n) ? std::ceil(m / 32.0) * std::ceil(n / 32.0) : 1.0;
         return 2.0 * rho_max * (m + n) * es + (rg + 1) * mn * es + rg * (double)(L + rcap) * 16 +
                tiles * PS * 8 + sizeof(FarStateDev) + sizeof(FarBlockDev) + rcap * 32.0 + L + 64;
     };
@@ -1311,7 +1307,6 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
             dw.kern = H[w]->kernel;
             dw.which = w;
             desc[nh * b + w] = dw;
-            kind[nh * b + w] = far_kind(m, n);
         }
         const double mn = (double)m * n;
         // first guess of the factor storage (the arena grows by half when it runs short)
@@ -1329,14 +1324,9 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
             return (int64_t)far[x][1] * far[x][3] > (int64_t)far[y][1] * far[y][3];
         });
         std::vector<FarBlockDev> dsort(ntot);
-        std::vector<int> ksort(ntot);
         for (int64_t i = 0; i < nfar; ++i)
-            for (int w = 0; w < nh; ++w) {
-                dsort[nh * i + w] = desc[nh * ord[i] + w];
-                ksort[nh * i + w] = kind[nh * ord[i] + w];
-            }
+            for (int w = 0; w < nh; ++w) dsort[nh * i + w] = desc[nh * ord[i] + w];
         desc.swap(dsort);
-        kind.swap(ksort);
     }
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
@@ -1344,7 +1334,8 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
         free_b = (size_t)p->opt.batch_bytes;
     }
 
-    // the aca phase of kind k runs on ks[k] (kind 3, the large faces, on the main far stream)
+    // the aca phase of launch class k (see aca_class below) runs on ks[k] (class 3, the faces in
+    // HBM, on the main far stream)
     const hipStream_t ks[4] = {p->far_streams[3], p->far_streams[2], p->far_streams[1], s0};
     enum { EV_BEGIN, EV_END, EV_F0, EV_F1, EV_K0, EV_K1, EV_K2, EV_K3, EV_S0, EV_S1, EV_S2, EV_S3, EV_J, EV_X,
            EV_T, EV_C, EV_P0, EV_P2, EV_N };
@@ -1406,7 +1397,7 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
     const double fe_bytes = mixed ? 8.0 : 16.0;   // one face element
     double fl_kind[4] = {0, 0, 0, 0};
     int launches_kind[4] = {0, 0, 0, 0};
-    // faces with a side above kMediumSide by kernel path (0 general, 1 one entry per thread,
+    // faces in HBM by kernel path (0 general, 1 one entry per thread,
     // 2 several entries per thread): device time, launches, algorithmic flops
     double ms_path[3] = {0, 0, 0}, fl_path[3] = {0, 0, 0};
     int launches_path[3] = {0, 0, 0};
@@ -1453,7 +1444,6 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
         }
         const std::pair<int64_t, int64_t> bt{bnext, blast};
         bnext = blast;
-        const int64_t base = bt.first;
         const int nb = (int)(bt.second - bt.first);
         std::vector<FarBlockDev> bdesc(desc.begin() + bt.first, desc.begin() + bt.second);
         int64_t uw_total = 0;
@@ -1550,44 +1540,40 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
             return true;
         };
 
-        // kind 3 first (large faces with a side above kMediumSide before the medium ones),
-        // then 2, 1, 0; larger faces first within a class
-        auto big = [&](int x) { return std::max(bdesc[x].m, bdesc[x].n) > kMediumSide; };
-        // large-face kernel path of a big face: 0 general (several entries per thread
-        // beyond the register paths), 2 several entries per thread, 1 one entry per thread
+        // kernel path of a face in HBM: 0 general (several entries per thread beyond the
+        // register paths), 2 several entries per thread, 1 one entry per thread
         const int tlx = p->opt.threads_large > 0 ? p->opt.threads_large : 512;
         auto path = [&](int x) {
             const int side = std::max(bdesc[x].m, bdesc[x].n);
             if (side <= tlx) return 1;
             return (tlx == 512 && side <= kFarMultiE * 512) ? 2 : 0;
         };
-        // one-entry faces with sides <= 256 under a larger workgroup size run with 256
-        // threads (two faces per CU) on the class-1 stream, beside the larger faces
-        auto small_big = [&](int x) {
-            return tlx > 256 && path(x) == 1 && std::max(bdesc[x].m, bdesc[x].n) <= 256;
-        };
-        auto prank = [&](int x) {
-            const int pth = path(x);
-            return pth == 0 ? 0 : pth == 2 ? 1 : small_big(x) ? 3 : 2;
-        };
-        // launch class of a block's face ACA (the stream it runs on)
-        auto aca_class = [&](int x) {
-            const int kd = kind[base + x];
-            if (kd != 3) return kd;
-            return !big(x) ? 2 : small_big(x) ? 1 : 3;
+        // launch groups, in launch order: faces in HBM by path (0, 2, 1, then the one-entry faces
+        // with sides <= 256 under a larger workgroup size, which run with 256 threads, two per
+        // CU, beside the larger ones), then the register classes from the largest side down
+        constexpr int kGroups = 4 + kFarRegClasses;
+        std::vector<int8_t> group(nb);
+        for (int x = 0; x < nb; ++x) {
+            const int rc = far_reg_class(bdesc[x].m, bdesc[x].n, mixed), pth = path(x);
+            const bool small_big = tlx > 256 && pth == 1 && std::max(bdesc[x].m, bdesc[x].n) <= 256;
+            group[x] = (int8_t)(rc >= 0 ? 4 + kFarRegClasses - 1 - rc : pth == 0 ? 0 : pth == 2 ? 1 : small_big ? 3 : 2);
+        }
+        auto reg_cls = [](int g) { return kFarRegClasses - 1 - (g - 4); };   // g >= 4
+        // stream (launch class) of a group: 3 the faces in HBM, 2 sides above 96 in registers and
+        // the 256-thread faces in HBM (the clusters halve from level to level, so a partition has
+        // few of one beside the other), 1 sides 33 to 96, 0 sides up to 32.  The runtime puts
+        // classes 1 and 0 on one hardware queue, where they and the Gram rows run in turn
+        auto aca_class = [&](int g) {
+            if (g < 4) return g == 3 ? 2 : 3;
+            const int side = kFarRegSide[reg_cls(g)];
+            return side > 96 ? 2 : side > 32 ? 1 : 0;
         };
         {
-            // launch order as one key per block: class (3 first), then for kind 3 the big
-            // faces first and among them the path rank, then m n descending; a stable sort
-            // keeps the block order among equal keys
+            // launch order: by group, then m n descending; a stable sort keeps the block order
+            // among equal keys
             std::vector<int64_t> okey(nb);
-            for (int x = 0; x < nb; ++x) {
-                const int kd = kind[base + x];
-                const bool bg = kd == 3 && big(x);
-                const int64_t mn = (int64_t)bdesc[x].m * bdesc[x].n;
-                okey[x] = ((int64_t)(3 - kd) << 40) | ((int64_t)(kd == 3 && !bg) << 36) |
-                          ((int64_t)(bg ? prank(x) : 0) << 32) | ((int64_t)0xFFFFFFFF - mn);
-            }
+            for (int x = 0; x < nb; ++x)
+                okey[x] = ((int64_t)group[x] << 40) | ((int64_t)0xFFFFFFFF - (int64_t)bdesc[x].m * bdesc[x].n);
             std::stable_sort(active.begin(), active.end(), [&](int x, int y) { return okey[x] < okey[y]; });
         }
         while (!active.empty()) {
@@ -1617,24 +1603,21 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
             grow_keep(ctx, W.hpool, (size_t)hused * es, (size_t)hprev * es, s0);
             grow_keep(ctx, W.fgpool, (size_t)fused * sizeof(double2), (size_t)fprev * sizeof(double2), s0);
             // the list is in launch order (sorted once before the first iteration; finished
-            // blocks leave in order)
-            int nbig = 0, nsb = 0, npath[3] = {0, 0, 0};
-            while (nbig < (int)active.size() && kind[base + active[nbig]] == 3 && big(active[nbig])) {
-                const int x = active[nbig++];
-                if (small_big(x)) ++nsb;
-                else ++npath[path(x)];
-            }
+            // blocks leave in order): first face and number of faces of each group
+            int gcnt[kGroups] = {}, gfirst[kGroups + 1] = {};
+            for (int x : active) ++gcnt[(int)group[x]];
+            for (int g = 0; g < kGroups; ++g) gfirst[g + 1] = gfirst[g] + gcnt[g];
             const int nact = (int)active.size();
             ms_prep += wall_ms_since(t_it);
             const auto t_launch = std::chrono::steady_clock::now();
             FarActive *ha = W.h_act.as<FarActive>();
             int64_t nchunk = 0, ntile = 0;
-            int cnt[4] = {0, 0, 0, 0};
+            int nexp = 0;   // faces with expand tiles (they come first)
             double fl_face = 0.0, by_face = 0.0;
             for (int a = 0; a < nact; ++a) {
                 const int lb = active[a];
                 const FarBlockDev &d = bdesc[lb];
-                const int kd = kind[base + lb];
+                const bool ex = far_expanded(d.m, d.n);
                 const int64_t mn = (int64_t)d.m * d.n;
                 FarActive A{};
                 A.b = lb;
@@ -1644,15 +1627,15 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
                 nchunk += (mn + kFarChunk - 1) / kFarChunk;
                 A.tile0 = ntile;
                 // with recompression every face is expanded again from its new factors
-                A.ntile = (kd == 3 || recomp) ? ((d.m + kFarTile - 1) / kFarTile) * ((d.n + kFarTile - 1) / kFarTile) : 0;
+                A.ntile = (ex || recomp) ? ((d.m + kFarTile - 1) / kFarTile) * ((d.n + kFarTile - 1) / kFarTile) : 0;
                 ntile += A.ntile;
-                cnt[kd]++;
+                nexp += ex;
                 ha[a] = A;
             }
             // small faces: one partial row each (their Gram row), after the expand tiles
             if (!recomp)
-                for (int a = cnt[3]; a < nact; ++a) ha[a].tile0 = ntile + (a - cnt[3]);
-            const int64_t nparts = recomp ? ntile : ntile + (nact - cnt[3]);
+                for (int a = nexp; a < nact; ++a) ha[a].tile0 = ntile + (a - nexp);
+            const int64_t nparts = recomp ? ntile : ntile + (nact - nexp);
             ensure(ctx, W.map_chunk, (size_t)std::max<int64_t>(nchunk, 1) * sizeof(int32_t));
             ensure(ctx, W.map_tile, (size_t)std::max<int64_t>(ntile, 1) * sizeof(int32_t));
             ensure(ctx, W.part, (size_t)std::max<int64_t>(nparts, 1) * PS * sizeof(double));
@@ -1660,9 +1643,7 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
                                           hipMemcpyHostToDevice, s0));
             const FarBatchDev bd = batch_dev(iter & 1);
             const FarActive *dact = W.act.as<FarActive>();
-            const int nlarge = recomp ? nact : cnt[3];
-            // act is ordered kind 3, 2, 1, 0
-            const int first[4] = {cnt[3] + cnt[2] + cnt[1], cnt[3] + cnt[2], cnt[3], 0};
+            const int nlarge = recomp ? nact : nexp;
             launch_far_map(bd, dact, nact, nlarge, s0);
             GACA_HIP_CHECK(hipEventRecord(ev[EV_F0], s0));
             launch_far_face(fk, p->g, p->f, bd, dact, nchunk, s0);
@@ -1682,50 +1663,38 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
             // reads (on ks[0], in order before the class-0 launches)
             if (copy_ev)
                 for (int k = 1; k < 4; ++k) GACA_HIP_CHECK(hipStreamWaitEvent(ks[k], ev[EV_C], 0));
-            // large faces: 512 threads and ~104 KB of LDS history, one face per CU (the
-            // longest face bounds the phase); medium faces (sides <= kMediumSide) 256 threads
-            // and 32 KB, several per CU, on the kind-2 stream, so that they do not hold whole
-            // CUs against the small-face kinds
-            int tl = p->opt.threads_large;
-            if (tl <= 0) tl = 512;
-            const int ts = p->opt.threads_small;
             // class k's launches run between EV_S0 + k and EV_K0 + k on ks[k] (after its waits)
             for (int k = 0; k < 4; ++k) GACA_HIP_CHECK(hipEventRecord(ev[EV_S0 + k], ks[k]));
-            int nl = 0;
-            for (int k = 3; k >= 0; --k) {
-                if (cnt[k] == 0) continue;
-                if (k == 3) {
-                    // big faces by path (general, several entries, one entry per thread),
-                    // one after the other on the kind-3 stream
-                    launch_far_aca(0, tl, P, bd, dact, npath[0], ks[3]);
-                    GACA_HIP_CHECK(hipEventRecord(ev[EV_P0], ks[3]));
-                    launch_far_aca(2, tl, P, bd, dact + npath[0], npath[2], ks[3]);
-                    GACA_HIP_CHECK(hipEventRecord(ev[EV_P2], ks[3]));
-                    launch_far_aca(1, tl, P, bd, dact + npath[0] + npath[2], npath[1], ks[3]);
-                    launch_far_aca(1, 256, P, bd, dact + npath[0] + npath[2] + npath[1], nsb, ks[1]);
-                    launch_far_aca(1, 256, P, bd, dact + nbig, cnt[3] - nbig, ks[2]);
-                    nl += (npath[0] > 0) + (npath[2] > 0) + (npath[1] > 0) + (nsb > 0) + (cnt[3] > nbig);
-                    continue;
-                }
-                if (k == 0 && ts <= 64) {
-                    // one wave per face: faces with m n <= 576 (after the larger ones) hold
-                    // nine register entries per lane instead of sixteen
-                    int a = first[0];
-                    while (a < first[0] + cnt[0] && (int64_t)bdesc[ha[a].b].m * bdesc[ha[a].b].n > 576) ++a;
-                    launch_far_aca_small(1024, 64, P, bd, dact + first[0], a - first[0], ks[0]);
-                    launch_far_aca_small(576, 64, P, bd, dact + a, first[0] + cnt[0] - a, ks[0]);
-                    nl += (a > first[0]) + (a < first[0] + cnt[0]);
-                } else {
-                    const int mnmax = k == 0 ? 1024 : k == 1 ? 2304 : 4096;
-                    launch_far_aca_small(mnmax, k == 0 ? ts : k == 1 ? 256 : 512, P, bd, dact + first[k],
-                                         cnt[k], ks[k]);
-                    ++nl;
-                }
-                if (!recomp) {
-                    launch_far_gram_small(bd, dact + first[k], cnt[k], ks[k]);
-                    ++nl;
-                }
+            int nl = 0, ccls[4] = {0, 0, 0, 0};
+            // faces in HBM by path (general, several entries, one entry per thread), one after
+            // the other on ks[3]: 512 threads and ~104 KB of LDS history, one face per CU
+            launch_far_aca(0, tlx, P, bd, dact, gcnt[0], ks[3]);
+            GACA_HIP_CHECK(hipEventRecord(ev[EV_P0], ks[3]));
+            launch_far_aca(2, tlx, P, bd, dact + gfirst[1], gcnt[1], ks[3]);
+            GACA_HIP_CHECK(hipEventRecord(ev[EV_P2], ks[3]));
+            launch_far_aca(1, tlx, P, bd, dact + gfirst[2], gcnt[2], ks[3]);
+            launch_far_aca(1, 256, P, bd, dact + gfirst[3], gcnt[3], ks[2]);
+            for (int g = 0; g < kGroups; ++g) {
+                if (gcnt[g] == 0) continue;
+                ++nl;
+                const int k = aca_class(g);
+                ccls[k] += gcnt[g];
+                if (g < 4) continue;
+                launch_far_aca_reg(reg_cls(g), P, bd, dact + gfirst[g], gcnt[g], ks[k]);
             }
+            // Gram rows of the faces that are not expanded, after the ACAs of their class
+            if (!recomp)
+                for (int k = 1; k >= 0; --k) {
+                    int g0 = kGroups, g1 = 0;
+                    for (int g = 4; g < kGroups; ++g)
+                        if (aca_class(g) == k && kFarRegSide[reg_cls(g)] <= kFarEmitSide) {
+                            g0 = std::min(g0, g);
+                            g1 = g + 1;
+                        }
+                    const int cn = gfirst[g1] - gfirst[g0];
+                    launch_far_gram_small(bd, dact + gfirst[g0], cn, ks[k]);
+                    nl += cn > 0;
+                }
             GACA_HIP_CHECK(hipGetLastError());
             for (int k = 0; k < 4; ++k) GACA_HIP_CHECK(hipEventRecord(ev[EV_K0 + k], ks[k]));
             for (int k = 0; k < 3; ++k) GACA_HIP_CHECK(hipStreamWaitEvent(s0, ev[EV_K0 + k], 0));
@@ -1764,20 +1733,16 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
             ms_phase[1] += elapsed(EV_F1, EV_J);
             ms_phase[2] += elapsed(EV_J, EV_X);
             ms_phase[3] += elapsed(EV_X, EV_T);
-            // launch classes by stream: 0, 1 (with the large faces of sides <= 256 when the
-            // large workgroup size is above 256), 2 (kind 2 and the medium large faces), 3 (the
-            // other large faces, sides above kMediumSide)
-            const int ccls[4] = {cnt[0], cnt[1] + nsb, cnt[2] + cnt[3] - nbig, nbig - nsb};
             for (int k = 0; k < 4; ++k)
                 if (ccls[k]) {
                     ms_kind[k] += elapsed(EV_S0 + k, EV_K0 + k);
                     launches_kind[k] += 1;
                 }
-            if (nbig > nsb) {
+            if (ccls[3]) {
                 // the path launches follow each other on ks[3]: path 0, path 2, path 1
-                if (npath[0]) { ms_path[0] += elapsed(EV_S0 + 3, EV_P0); launches_path[0] += 1; }
-                if (npath[2]) { ms_path[2] += elapsed(EV_P0, EV_P2); launches_path[2] += 1; }
-                if (npath[1]) { ms_path[1] += elapsed(EV_P2, EV_K0 + 3); launches_path[1] += 1; }
+                if (gcnt[0]) { ms_path[0] += elapsed(EV_S0 + 3, EV_P0); launches_path[0] += 1; }
+                if (gcnt[1]) { ms_path[2] += elapsed(EV_P0, EV_P2); launches_path[2] += 1; }
+                if (gcnt[2]) { ms_path[1] += elapsed(EV_P2, EV_K0 + 3); launches_path[1] += 1; }
             }
             launches_phase[0] += 1;
             launches_phase[1] += nl;
@@ -1796,7 +1761,6 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
                 const int code = hs_[2 * a], rho = hs_[2 * a + 1];
                 const double mn = (double)d.m * d.n;
                 const int ell = ell_h[lb];
-                const int kd = kind[base + lb];
                 if (code & 1) {
                     FarCopy c{};
                     c.b = lb;
@@ -1809,22 +1773,21 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
                     ell_h[lb] = ell + 1;
                     hcur[lb] = -1;
                     fcur[lb] = -1;
-                    // face ACA: kind 3 corrects rows / columns from the factor history and
-                    // forms the cross terms of |S|^2, 2 (m + n) q complex MACs at step q; the
-                    // LDS kinds update R and S in place (2 m n per step) and form the Gram row
-                    if (kd == 3) {
-                        const double f = 8.0 * (d.m + d.n) * (double)rho * (rho - 1.0);
-                        fl_phase[1] += f;
-                        const int ac = aca_class(lb);
-                        fl_kind[ac] += f;
-                        if (ac == 3) fl_path[path(lb)] += f;
+                    // face ACA: the faces in HBM correct rows and columns from the factor
+                    // history and form the cross terms of |S|^2, 2 (m + n) q complex MACs at step
+                    // q; the faces in registers update R in place, m n complex MACs per step
+                    const int g = group[lb], ac = aca_class(g);
+                    const double f = g < 4 ? 8.0 * (d.m + d.n) * (double)rho * (rho - 1.0) : 8.0 * mn * rho;
+                    fl_phase[1] += f;
+                    fl_kind[ac] += f;
+                    if (ac == 3) fl_path[path(lb)] += f;
+                    if (far_expanded(d.m, d.n)) {
                         fl_phase[2] += 8.0 * mn * (rho + ell);
                         // U, W read, H_l written, the previous faces read once (Gram row)
                         by_phase[2] += ((double)rho * (d.m + d.n) + mn * (ell + 1.0)) * fe_bytes;
                     } else {
-                        const double f = 8.0 * mn * (2.0 * rho + ell);
-                        fl_phase[1] += f;
-                        fl_kind[kd] += f;
+                        fl_phase[1] += 8.0 * mn * ell;   // Gram row
+                        fl_kind[ac] += 8.0 * mn * ell;
                     }
                     const double qpe = qpe_of(d);
                     fl_phase[3] += (double)L * qpe * f_eval_of(d.kern) + 16.0 * L * ell + 8.0 * (ell + 1.0) * (ell + 1.0);
@@ -2301,7 +2264,7 @@ static bool build_ops(gaca_problem *p, const std::vector<gaca_kernel> &kernels,
 }  // extern "C"
 
 namespace {
-const int kTuneCand[][2] = {{512, 128}, {1024, 128}, {512, 64}, {256, 128}};
+const int kTuneCand[][2] = {{512, 128}, {1024, 128}, {256, 128}};
 
 std::string tune_key(const gaca_problem *p, const std::vector<gaca_kernel> &kernels) {
     char buf[512];
