@@ -60,6 +60,24 @@ void launch_eval_gp1(int op, const GeoDev &g, const QuadDev &q, const FreqDev &f
                      const int32_t *rows, const int32_t *cols, const int32_t *ks,
                      const int32_t *far, double2 *out, hipStream_t st);
 
+// The same near field by triangle pairs (csrc/near_gp1.hip): pairs (ti, tj) sorted by ti, then tj
+// (row ti: rowptr[ti] .. rowptr[ti + 1]), and the indices of the pairs of each class.
+enum Gp1Class : int32_t { GP1_FAR = 0, GP1_MID = 1, GP1_NEAR = 2, GP1_VERTEX = 3 /* 3, 4, 5: 1, 2, 3 shared vertices */ };
+constexpr int kGp1Classes = 6;
+struct Gp1Pairs {
+    int64_t np;
+    const int2 *pairs;
+    const int64_t *rowptr;
+    const int32_t *list;
+    int64_t first[kGp1Classes + 1];   // class c: list[first[c] .. first[c + 1])
+};
+constexpr int64_t kGp1Slot = 10 * 16;   // bytes per pair and frequency of the pair buffer
+void launch_gp1_classes(const GeoDev &g, const int2 *pairs, int64_t np, uint8_t *cls, hipStream_t st);
+// buf: np * nfc slots; the frequencies go in chunks of nfc
+void launch_near_gp1_pairs(int op, const GeoDev &g, const QuadDev &q, const FreqDev &f, const Gp1Pairs &P,
+                           double2 *buf, int nfc, const NearPair *vp, int64_t nvp,
+                           const NearBlockDev *blocks, double2 *out64, hipStream_t st);
+
 // Near field: every pair of one tier, all frequencies, FP64 compute, stored as double2
 // (out64) or float2 (out32).
 void launch_near(int kernel, int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f,

@@ -421,6 +421,11 @@ struct gaca_problem {
     std::vector<double> patch_prefix;    // prefix sums of the patch sizes in tree order
     double p1_near_points = 0.0;         // quadrature points of the near field per frequency
     DevBuf d_p1i;
+    // Galerkin P1: the triangle pairs of the near field and the buffer of their integrals (kept
+    // for the problem's builds; nfc frequencies at a time, 0: no pair list, entry by entry)
+    DevBuf d_gp1_pairs, d_gp1_rowptr, d_gp1_list, d_gp1_buf;
+    Gp1Pairs gp1{};
+    int gp1_nfc = 0;
     ClusterTree tree;
     Partition part;
     int32_t L = 0;
@@ -959,6 +964,95 @@ static void upload_problem_p1(gaca_problem *p) {
     set_leaves(p);
 }
 
+// Triangle pairs of the Galerkin P1 near field: every (ti, tj) with a near vertex pair on it,
+// grouped by the class that the device finds (the rules' comparisons stay in one place).  Under
+// a memory cap, or where the memory does not suffice, there is no list and the near field is
+// evaluated entry by entry.
+static void upload_gp1_pairs(gaca_problem *p) {
+    gaca_context *ctx = p->ctx;
+    if (ctx->limit) return;
+    const int64_t T = p->mesh.M;
+    // column clusters met by each row cluster, and the triangles of a cluster's patches
+    std::map<std::pair<int64_t, int64_t>, std::vector<std::pair<int64_t, int64_t>>> cols_of;
+    std::map<std::pair<int64_t, int64_t>, std::vector<int32_t>> tris_of;
+    for (const auto &nb : p->part.near) {
+        cols_of[{nb[0], nb[1]}].push_back({nb[2], nb[3]});
+        for (int s = 0; s < 4; s += 2) {
+            auto &t = tris_of[{nb[s], nb[s + 1]}];
+            if (!t.empty()) continue;
+            t.assign(p->ptri.begin() + p->pptr[nb[s]], p->ptri.begin() + p->pptr[nb[s] + nb[s + 1]]);
+            std::sort(t.begin(), t.end());
+            t.erase(std::unique(t.begin(), t.end()), t.end());
+        }
+    }
+    std::vector<std::vector<const std::vector<int32_t> *>> sets(T);
+    for (const auto &rc : cols_of)
+        for (int32_t ti : tris_of[rc.first])
+            for (const auto &c : rc.second) sets[ti].push_back(&tris_of[c]);
+    std::vector<int64_t> rowptr(T + 1, 0);
+    std::vector<int2> pairs;
+    std::vector<int32_t> mark(T, -1), row;
+    row.reserve(T);
+    for (int64_t ti = 0; ti < T; ++ti) {
+        row.clear();
+        for (const auto *set : sets[ti])
+            for (int32_t tj : *set)
+                if (mark[tj] != ti) {
+                    mark[tj] = (int32_t)ti;
+                    row.push_back(tj);
+                }
+        if ((int64_t)row.size() * 8 > T) {   // a full row: in order by its marks
+            for (int32_t tj = 0; tj < T; ++tj)
+                if (mark[tj] == ti) pairs.push_back(make_int2((int)ti, tj));
+        } else {
+            std::sort(row.begin(), row.end());
+            for (int32_t tj : row) pairs.push_back(make_int2((int)ti, tj));
+        }
+        rowptr[ti + 1] = (int64_t)pairs.size();
+    }
+    const int64_t np = (int64_t)pairs.size();
+    if (np == 0 || np > INT32_MAX) return;
+    try {
+        DevBuf cls;
+        p->d_gp1_pairs.upload(ctx, pairs);
+        p->d_gp1_rowptr.upload(ctx, rowptr);
+        cls.alloc(ctx, np);
+        launch_gp1_classes(p->g, p->d_gp1_pairs.as<int2>(), np, cls.as<uint8_t>(), ctx->stream);
+        GACA_HIP_CHECK(hipGetLastError());
+        GACA_HIP_CHECK(hipStreamSynchronize(ctx->stream));
+        std::vector<uint8_t> hc(np);
+        GACA_HIP_CHECK(hipMemcpy(hc.data(), cls.ptr, np, hipMemcpyDeviceToHost));
+        int64_t *first = p->gp1.first;
+        std::fill(first, first + kGp1Classes + 1, (int64_t)0);
+        for (uint8_t c : hc) ++first[c + 1];
+        for (int c = 0; c < kGp1Classes; ++c) first[c + 1] += first[c];
+        std::vector<int32_t> list(np);
+        std::vector<int64_t> at(first, first + kGp1Classes);
+        for (int64_t t = 0; t < np; ++t) list[at[hc[t]]++] = (int32_t)t;
+        p->d_gp1_list.upload(ctx, list);
+        // as many frequencies as 2 GiB or an eighth of the free memory hold
+        size_t fb = 0, tb = 0;
+        if (hipMemGetInfo(&fb, &tb) != hipSuccess) {
+            (void)hipGetLastError();
+            fb = 0;
+        }
+        const int64_t budget = std::min<int64_t>((int64_t)2 << 30, (int64_t)(fb / 8));
+        p->gp1_nfc = (int)std::min<int64_t>(p->f.L_eval, budget / (np * kGp1Slot));
+    } catch (const Error &) {   // the entry-by-entry kernel needs none of this
+        p->gp1_nfc = 0;
+    }
+    if (p->gp1_nfc == 0) {
+        p->d_gp1_pairs.release();
+        p->d_gp1_rowptr.release();
+        p->d_gp1_list.release();
+        return;
+    }
+    p->gp1.np = np;
+    p->gp1.pairs = p->d_gp1_pairs.as<int2>();
+    p->gp1.rowptr = p->d_gp1_rowptr.as<int64_t>();
+    p->gp1.list = p->d_gp1_list.as<int32_t>();
+}
+
 static void upload_freq(gaca_problem *p) {
     std::vector<double> fr(2 * p->L);
     for (int l = 0; l < p->L; ++l) {
@@ -1026,6 +1120,7 @@ gaca_status gaca_problem_create(gaca_context *ctx, const double *xyz, int64_t nv
         GACA_HIP_CHECK(hipSetDevice(ctx->device));
         upload_problem(p.get());
         upload_freq(p.get());
+        if (scheme == GACA_GALERKIN_P1) upload_gp1_pairs(p.get());
         *out = p.release();
     });
 }
@@ -2192,9 +2287,23 @@ static bool build_ops(gaca_problem *p, const std::vector<gaca_kernel> &kernels,
             if (p->scheme == GACA_COLLOCATION_P1)
                 launch_near_p1(p->g, p->q, p->f, p->d_pairs[0].as<NearPair>(), p->npairs[0],
                                p->d_nblocks.as<NearBlockDev>(), n64, st);
-            if (p->scheme == GACA_GALERKIN_P1)
-                launch_near_gp1(kernels[w] == GACA_HYP ? 0 : 1, p->g, p->q, p->f, p->d_pairs[0].as<NearPair>(),
-                                p->npairs[0], p->d_nblocks.as<NearBlockDev>(), n64, st);
+            if (p->scheme == GACA_GALERKIN_P1) {
+                const int op = kernels[w] == GACA_HYP ? 0 : 1;
+                if (p->gp1_nfc > 0 && !p->d_gp1_buf.ptr) {
+                    try {
+                        p->d_gp1_buf.alloc(ctx, (size_t)p->gp1.np * p->gp1_nfc * kGp1Slot);
+                    } catch (const Error &) {
+                        p->gp1_nfc = 0;
+                    }
+                }
+                if (p->gp1_nfc > 0)
+                    launch_near_gp1_pairs(op, p->g, p->q, p->f, p->gp1, p->d_gp1_buf.as<double2>(), p->gp1_nfc,
+                                          p->d_pairs[0].as<NearPair>(), p->npairs[0],
+                                          p->d_nblocks.as<NearBlockDev>(), n64, st);
+                else
+                    launch_near_gp1(op, p->g, p->q, p->f, p->d_pairs[0].as<NearPair>(), p->npairs[0],
+                                    p->d_nblocks.as<NearBlockDev>(), n64, st);
+            }
             for (int t = 0; t < kNumTiers && !p->p1(); ++t) {
                 if (p->scheme == GACA_GALERKIN_P0)
                     launch_near_galerkin(t, p->g, p->q, p->f, p->d_pairs[t].as<NearPair>(),
