@@ -14,7 +14,8 @@
 // pairs, until a sweep rotates no pair with |k_p^H k_q| > 1e-15 ||k_p|| ||k_q||.  All in
 // FP64 (the mixed path's FP32 factors are widened and the results rounded back).
 // Faces of rank 1 are already in that form; faces of rank above kRecMaxRank are kept as
-// computed.  One workgroup per face, grid-stride over the active faces, each workgroup with
+// computed.  Faces with sides up to 32 take the LDS kernel below; for the others one workgroup per
+// face, grid-stride over the active faces, each workgroup with
 // its own slot of 6 kRecMaxRank^2 complex doubles of workspace (R_U, R_W, K, V, A_U, B_W);
 // the old factors are copied to the face's H slot (m n >= rho max(m, n)) while the new
 // ones are written in place.
@@ -267,12 +268,260 @@ __global__ void __launch_bounds__(256) far_recompress_kernel(AcaParams P, FarBat
     }
 }
 
+// 1 / x and 1 / sqrt(x) from the hardware estimates, two Newton steps each (1 ulp for normal x)
+__device__ __forceinline__ double rcp2(double x) {
+    double t = __builtin_amdgcn_rcp(x);
+    t = fma(t, fma(-x, t, 1.0), t);
+    return fma(t, fma(-x, t, 1.0), t);
+}
+__device__ __forceinline__ double rsq2(double x) {
+    double t = __builtin_amdgcn_rsq(x);
+    t = fma(0.5 * t, fma(-x * t, t, 1.0), t);
+    return fma(0.5 * t, fma(-x * t, t, 1.0), t);
+}
+
+// The same for small faces (m, n <= RM): two waves per face with everything in LDS.  The general
+// kernel spends its time waiting: its matrices lie in HBM, one workgroup per CU works through a
+// chain of short loops.  Here one wave prepares each factor, a round of the Jacobi iteration
+// rotates all its pairs at once (eight lanes a pair) with one barrier, and 4 RM^2 16 bytes of LDS
+// let four (RM = 24) or two (RM = 32) faces share a CU.  What bounds it now is the chain of a round
+// (dot products, rotation, update).  1614 faces of up to 24 x 24, rank 21 before the truncation
+// (768-triangle cube): 336 us a launch, in the general kernel 2570 us; one wave per face
+// took 402 us, a launch each for ranks up to 16 and above 500 us (few faces are below).
+template <bool MIXED, int RM>
+__global__ void __launch_bounds__(128) far_recompress_small_kernel(AcaParams P, FarBatchDev bd,
+                                                                   const FarActive *act) {
+    using FT = rface_t<MIXED>;
+    constexpr int LD = RM + 1;   // column stride: no power of two banks apart
+    constexpr int LP = 8;                 // lanes per pair (at most 16 pairs)
+    static_assert(RM <= 32, "sixteen pairs of columns a round");
+    const int tid = threadIdx.x, half = tid >> 6, hl = tid & 63;
+    const int b = act[blockIdx.x].b;
+    const int rho = bd.st[b].rho;
+    if (rho < 2) return;
+    const FarBlockDev B = bd.blk[b];
+    const int m = B.m, n = B.n;
+    FT *U = reinterpret_cast<FT *>(bd.uw) + B.uw_off;
+    FT *W = U + (int64_t)B.rho_max * m;
+    __shared__ double2 R2[2][RM * LD], K[RM * LD], V[RM * LD];
+    __shared__ double dsc[2][RM], sig2[RM];
+    __shared__ int order[RM];
+    // the factors staged in K and V (rows of stride LD), a wave for each
+    double2 *F = half ? V : K, *G = R2[half];
+    const int len = half ? n : m;
+    {
+        const FT *src = half ? W : U;
+        for (int e = hl; e < rho * len; e += 64) {
+            const int p = e / len;
+            F[p * LD + e - p * len] = to_d2(src[e]);
+        }
+    }
+    __syncthreads();
+    // Gram matrix G[q LD + p] = sum_i conj(F[p][i]) F[q][i], p <= q
+    for (int e = hl; e < rho * (rho + 1) / 2; e += 64) {
+        int q = (int)((sqrtf(8.0f * e + 1.0f) - 1.0f) * 0.5f);
+        while ((q + 1) * (q + 2) / 2 <= e) ++q;
+        while (q * (q + 1) / 2 > e) --q;
+        const int p = e - q * (q + 1) / 2;
+        double2 s = make_double2(0.0, 0.0);
+#pragma unroll 4
+        for (int i = 0; i < len; ++i) s = cadd(s, cconjmul(F[p * LD + i], F[q * LD + i]));
+        G[q * LD + p] = s;
+    }
+    __syncthreads();
+    // Cholesky factor of the column-scaled matrix, a lane per column
+    if (hl < rho) dsc[half][hl] = sqrt(fmax(G[hl * LD + hl].x, 0.0));
+    __syncthreads();
+    if (hl < rho)
+        for (int p = 0; p <= hl; ++p) {
+            const double s = dsc[half][p] * dsc[half][hl];
+            const double2 g = G[hl * LD + p];
+            G[hl * LD + p] = s > 0.0 ? make_double2(g.x / s, g.y / s) : make_double2(0.0, 0.0);
+        }
+    for (int j = 0; j < rho; ++j) {
+        __syncthreads();
+        double2 v = make_double2(0.0, 0.0);
+        if (hl >= j && hl < rho) {
+            v = G[hl * LD + j];
+#pragma unroll 4
+            for (int k = 0; k < j; ++k) v = csub(v, cconjmul(G[j * LD + k], G[hl * LD + k]));
+        }
+        const double a = __shfl(v.x, j, 64);
+        const double r = a > 1e-14 ? sqrt(a) : 0.0;
+        if (hl >= j && hl < rho)
+            G[hl * LD + j] = hl == j ? make_double2(r, 0.0)
+                                     : r > 0.0 ? make_double2(v.x / r, v.y / r) : make_double2(0.0, 0.0);
+    }
+    __syncthreads();
+    if (hl < rho)
+        for (int p = 0; p < rho; ++p) {
+            const double2 g = G[hl * LD + p];
+            G[hl * LD + p] = p > hl ? make_double2(0.0, 0.0) : make_double2(g.x * dsc[half][hl], g.y * dsc[half][hl]);
+        }
+    __syncthreads();
+    const double2 *RU = R2[0], *RW = R2[1];
+    // K = R_U R_W^T, V = I (columns of stride LD)
+    for (int e = tid; e < rho * rho; e += 128) {
+        const int q = e / rho, p = e - q * rho;
+        double2 s = make_double2(0.0, 0.0);
+        for (int k = max(p, q); k < rho; ++k) s = cadd(s, cmul_d(RU[k * LD + p], RW[k * LD + q]));
+        K[q * LD + p] = s;
+        V[q * LD + p] = make_double2(p == q ? 1.0 : 0.0, 0.0);
+    }
+    __syncthreads();
+    // one-sided Jacobi: round-robin pairs over rp = rho rounded up to even, LP lanes a pair
+    const int rp = rho + (rho & 1), pr = tid / LP, sub = tid % LP;
+    for (int sweep = 0; sweep < 40; ++sweep) {
+        bool any = false;
+        for (int round = 0; round < rp - 1; ++round) {
+            auto at = [&](int pos) {
+                const int t = pos - 1 + round;
+                return pos == 0 ? 0 : 1 + (t >= rp - 1 ? t - (rp - 1) : t);
+            };
+            int p = pr < rp / 2 ? at(pr) : 0, q = pr < rp / 2 ? at(rp - 1 - pr) : rho;
+            if (p > q) {
+                const int t = p;
+                p = q;
+                q = t;
+            }
+            const bool on = q < rho;   // not a padding column
+            double al = 0.0, be = 0.0, gr = 0.0, gi = 0.0;
+            if (on)
+#pragma unroll 4
+                for (int i = sub; i < rho; i += LP) {
+                    const double2 kp = K[p * LD + i], kq = K[q * LD + i];
+                    al += cabs2(kp);
+                    be += cabs2(kq);
+                    const double2 t = cconjmul(kp, kq);
+                    gr += t.x;
+                    gi += t.y;
+                }
+            // sums over the pair's eight lanes
+            al += dpp_d<0xB1>(al);
+            be += dpp_d<0xB1>(be);
+            gr += dpp_d<0xB1>(gr);
+            gi += dpp_d<0xB1>(gi);
+            al += dpp_d<0x4E>(al);
+            be += dpp_d<0x4E>(be);
+            gr += dpp_d<0x4E>(gr);
+            gi += dpp_d<0x4E>(gi);
+            al += dpp_d<0x141>(al);
+            be += dpp_d<0x141>(be);
+            gr += dpp_d<0x141>(gr);
+            gi += dpp_d<0x141>(gi);
+            const double g2 = gr * gr + gi * gi, ig = g2 > 0.0 ? rsq2(g2) : 0.0, gab = g2 * ig;
+            const bool rot = on && gab > 1e-15 * __builtin_amdgcn_sqrt(al * be);
+            if (rot) {
+                any = true;
+                const double2 ph = make_double2(gr * ig, -gi * ig);   // e^{-i phi}
+                const double zeta = 0.5 * (be - al) * ig;
+                const double z1 = 1.0 + zeta * zeta;
+                const double tt = (zeta >= 0.0 ? 1.0 : -1.0) * (z1 < 1e300 ? rcp2(fabs(zeta) + z1 * rsq2(z1)) : 0.5 / fabs(zeta));
+                const double c = rsq2(1.0 + tt * tt), s = c * tt;
+#pragma unroll 4
+                for (int i = sub; i < rho; i += LP) {
+                    const double2 kp = K[p * LD + i], kq = cmul_d(K[q * LD + i], ph);
+                    const double2 vp = V[p * LD + i], vq = cmul_d(V[q * LD + i], ph);
+                    K[p * LD + i] = make_double2(c * kp.x - s * kq.x, c * kp.y - s * kq.y);
+                    K[q * LD + i] = make_double2(s * kp.x + c * kq.x, s * kp.y + c * kq.y);
+                    V[p * LD + i] = make_double2(c * vp.x - s * vq.x, c * vp.y - s * vq.y);
+                    V[q * LD + i] = make_double2(s * vp.x + c * vq.x, s * vp.y + c * vq.y);
+                }
+            }
+            __syncthreads();
+        }
+        if (!__syncthreads_or(any)) break;
+    }
+    // singular values, order by decreasing value (ties: index), truncation
+    __syncthreads();
+    if (tid < rho) {
+        double s2 = 0.0;
+        for (int i = 0; i < rho; ++i) s2 += cabs2(K[tid * LD + i]);
+        sig2[tid] = s2;
+    }
+    __syncthreads();
+    if (tid < rho) {
+        int r = 0;
+        for (int x = 0; x < rho; ++x) r += sig2[x] > sig2[tid] || (sig2[x] == sig2[tid] && x < tid);
+        order[r] = tid;
+    }
+    __syncthreads();
+    double tot = 0.0;
+    for (int r = 0; r < rho; ++r) tot += sig2[order[r]];
+    const double lim2 = P.eps_aca * P.eps_aca * (bd.st[b].ref2 + tot);
+    int rk = rho;
+    double tail = 0.0;
+    while (rk > 1 && tail + sig2[order[rk - 1]] <= lim2) {
+        tail += sig2[order[rk - 1]];
+        --rk;
+    }
+    // A_U = R_W^T V_r over V and B_W = R_U^T conj((K V)_r) Sigma_r^{-2} over K (rho x rk)
+    constexpr int PER = (RM * RM + 127) / 128;
+    double2 au[PER], bw[PER];
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        const int e = tid + 128 * t;
+        au[t] = bw[t] = make_double2(0.0, 0.0);
+        if (e < rho * rk) {
+            const int c = e / rho, k = e - c * rho, oc = order[c];
+            for (int q = 0; q <= k; ++q) {
+                au[t] = cadd(au[t], cmul_d(RW[k * LD + q], V[oc * LD + q]));
+                bw[t] = cadd(bw[t], cmul_d(RU[k * LD + q], conj_d2(K[oc * LD + q])));
+            }
+            const double is2 = 1.0 / sig2[oc];
+            bw[t].x *= is2;
+            bw[t].y *= is2;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        const int e = tid + 128 * t;
+        if (e < rho * rk) {
+            const int c = e / rho, k = e - c * rho;
+            V[c * LD + k] = au[t];
+            K[c * LD + k] = bw[t];
+        }
+    }
+    __syncthreads();
+    // U' = U A_U and W' = W B_W: a lane holds row hl of the old factor while it writes the new
+    FT *out = half ? W : U;
+    const double2 *Tm = half ? K : V;
+    if (hl < len) {
+        double2 f[RM];
+#pragma unroll
+        for (int k = 0; k < RM; ++k) f[k] = k < rho ? to_d2(out[k * len + hl]) : make_double2(0.0, 0.0);
+        for (int c = 0; c < rk; ++c) {
+            double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
+            for (int k = 0; k < RM; ++k)
+                if (k < rho) acc = cadd(acc, cmul_d(f[k], Tm[c * LD + k]));
+            out[c * len + hl] = from_d2<FT>(acc);
+        }
+    }
+    if (tid == 0) bd.st[b].rho = rk;
+}
+
 void launch_far_recompress(const AcaParams &P, const FarBatchDev &bd, const FarActive *act,
                            int nact, double2 *ws, int nslot, hipStream_t st) {
     if (nact <= 0) return;
     const int g = nact < nslot ? nact : nslot;
     if (bd.mixed) far_recompress_kernel<true><<<g, 256, 0, st>>>(P, bd, act, nact, ws);
     else far_recompress_kernel<false><<<g, 256, 0, st>>>(P, bd, act, nact, ws);
+}
+
+template <bool MX>
+static void small_dispatch(int side, const AcaParams &P, const FarBatchDev &bd, const FarActive *act, int nact,
+                           hipStream_t st) {
+    if (side <= 24) far_recompress_small_kernel<MX, 24><<<nact, 128, 0, st>>>(P, bd, act);
+    else far_recompress_small_kernel<MX, 32><<<nact, 128, 0, st>>>(P, bd, act);
+}
+
+void launch_far_recompress_small(int side, const AcaParams &P, const FarBatchDev &bd,
+                                 const FarActive *act, int nact, hipStream_t st) {
+    if (nact <= 0) return;
+    if (bd.mixed) small_dispatch<true>(side, P, bd, act, nact, st);
+    else small_dispatch<false>(side, P, bd, act, nact, st);
 }
 
 }  // namespace gaca

@@ -173,6 +173,9 @@ constexpr int64_t kRecSlot = 6 * (int64_t)kRecMaxRank * kRecMaxRank;
 constexpr int kRecSlots = 256;   // concurrent faces (workgroups) of the recompression
 void launch_far_recompress(const AcaParams &P, const FarBatchDev &bd, const FarActive *act,
                            int nact, double2 *ws, int nslot, hipStream_t st);
+// the same for faces with both sides <= side <= 32, one wave and no workspace each
+void launch_far_recompress_small(int side, const AcaParams &P, const FarBatchDev &bd,
+                                 const FarActive *act, int nact, hipStream_t st);
 // Gram rows of the faces without expand tiles into their single partial row (FarActive::tile0)
 void launch_far_gram_small(const FarBatchDev &bd, const FarActive *act, int nact, hipStream_t st);
 void launch_far_tail(int kernel, const GeoDev &g, const FreqDev &f, const AcaParams &P,

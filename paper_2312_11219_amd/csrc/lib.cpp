@@ -1802,8 +1802,13 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
                 copy_ev = true;
             }
             if (recomp) {
-                launch_far_recompress(P, bd, dact, nact, W.rec_ws.as<double2>(), kRecSlots, s0);
-                ++n_launch;
+                // the classes of sides up to 32 (the last groups) one wave per face, in LDS
+                constexpr int g32 = 4 + kFarRegClasses - 2, g24 = g32 + 1;
+                static_assert(kFarRegSide[1] == 32 && kFarRegSide[0] == 24, "sides of the last two groups");
+                launch_far_recompress(P, bd, dact, gfirst[g32], W.rec_ws.as<double2>(), kRecSlots, s0);
+                launch_far_recompress_small(32, P, bd, dact + gfirst[g32], gcnt[g32], s0);
+                launch_far_recompress_small(24, P, bd, dact + gfirst[g24], gcnt[g24], s0);
+                n_launch += (gfirst[g32] > 0) + (gcnt[g32] > 0) + (gcnt[g24] > 0);
             }
             launch_far_expand(bd, dact, ntile, s0);
             GACA_HIP_CHECK(hipEventRecord(ev[EV_X], s0));
