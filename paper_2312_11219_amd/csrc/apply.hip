@@ -1,4 +1,4 @@
-// Reordered product eq. (product) of the compressed operator on the VALU:
+// Reordered product eq. (product) of the compressed operator:
 //   SUM:      Y[:, b] = sum_l C(s_l) X_l[:, b]
 //             far blocks: z_l = W_l^T (sum_k f_l[k] X_k[tau]),  y_b = sum_l U_l z_l
 //             near blocks: Y[sigma] += sum_k N_k X_k[tau]
@@ -46,60 +46,36 @@ void *scratch_address(int device) {
     return g_scratch_addr[device];
 }
 
-// Per-block workspace offsets of the VALU apply from the block metadata (what the host
-// computes for the allocated workspace): z_off = prefix of sum_rho * nrhs (SUM) or
-// sum_rho * L * nrhs (PER_FREQ), t_off = prefix of min(rank, cb) * n * nrhs (SUM; 0 else),
-// y_off = prefix of m * nrhs.  One workgroup: each thread sums a contiguous run of blocks,
+// Per-block offsets of z from the block metadata (what the host computes for the allocated
+// workspace): prefix of sum_rho * nrhs (SUM) or sum_rho * L * nrhs (PER_FREQ).
+// One workgroup: each thread sums a contiguous run of blocks,
 // the run totals are scanned in LDS, then each thread writes its run's prefixes.
-__global__ void __launch_bounds__(1024) apply_offsets_kernel(ApplyDev a, int mode, int cb,
-                                                             int64_t *zoff, int64_t *toff,
-                                                             int64_t *yoff) {
-    __shared__ int64_t sz[1024], st[1024], sy[1024];
+__global__ void __launch_bounds__(1024) apply_offsets_kernel(ApplyDev a, int mode, int64_t *zoff) {
+    __shared__ int64_t sz[1024];
     const int nb = a.nfar, t = threadIdx.x;
     const int per = (nb + 1023) / 1024;
     const int b0 = min(nb, t * per), b1 = min(nb, b0 + per);
     const int64_t zmul = mode == 0 ? a.nrhs : (int64_t)a.L * a.nrhs;
-    int64_t z = 0, tt = 0, y = 0;
-    for (int b = b0; b < b1; ++b) {
-        z += (int64_t)a.meta[b].sum_rho * zmul;
-        if (mode == 0) tt += (int64_t)min(a.meta[b].rank, cb) * a.far4[4 * b + 3] * a.nrhs;
-        y += (int64_t)a.far4[4 * b + 1] * a.nrhs;
-    }
+    int64_t z = 0;
+    for (int b = b0; b < b1; ++b) z += a.meta[b].sum_rho * zmul;
     sz[t] = z;
-    st[t] = tt;
-    sy[t] = y;
     __syncthreads();
-    // inclusive scan of the run totals (Hillis-Steele)
     for (int d = 1; d < 1024; d <<= 1) {
-        int64_t vz = 0, vt = 0, vy = 0;
-        if (t >= d) {
-            vz = sz[t - d];
-            vt = st[t - d];
-            vy = sy[t - d];
-        }
+        const int64_t vz = t >= d ? sz[t - d] : 0;
         __syncthreads();
         sz[t] += vz;
-        st[t] += vt;
-        sy[t] += vy;
         __syncthreads();
     }
     z = sz[t] - z;
-    tt = st[t] - tt;
-    y = sy[t] - y;
     for (int b = b0; b < b1; ++b) {
         zoff[b] = z;
-        toff[b] = tt;
-        yoff[b] = y;
-        z += (int64_t)a.meta[b].sum_rho * zmul;
-        if (mode == 0) tt += (int64_t)min(a.meta[b].rank, cb) * a.far4[4 * b + 3] * a.nrhs;
-        y += (int64_t)a.far4[4 * b + 1] * a.nrhs;
+        z += a.meta[b].sum_rho * zmul;
     }
 }
 
-void launch_apply_offsets(const ApplyDev &a, int mode, int cb, int64_t *zoff, int64_t *toff,
-                          int64_t *yoff, hipStream_t st) {
-    if (a.nfar <= 0) return;
-    apply_offsets_kernel<<<1, 1024, 0, st>>>(a, mode, cb, zoff, toff, yoff);
+void launch_apply_offsets(const ApplyDev &a, int mode, int64_t *zoff, hipStream_t st) {
+    if (a.nfar < 1) return;
+    apply_offsets_kernel<<<1, 1024, 0, st>>>(a, mode, zoff);
 }
 
 template <class XT>
@@ -115,297 +91,27 @@ __global__ void permute_x_kernel(const XT *X, XT *Xp, const int64_t *perm, int L
     Xp[t] = X[(l * M + perm[p]) * nrhs + c];
 }
 
+__device__ __forceinline__ int64_t readlane_i64(int64_t v, int l) {
+    const int lo = __builtin_amdgcn_readlane((int)v, l), hi = __builtin_amdgcn_readlane((int)(v >> 32), l);
+    return ((int64_t)hi << 32) | (unsigned)lo;
+}
+
+// sum over the eight lanes of a group, in every one of them (FP64 partial sums)
 template <class XT>
-__global__ void scatter_y_kernel(const XT *Yp, XT *Y, const int64_t *perm, int nl, int64_t M,
-                                 int nrhs) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t total = (int64_t)nl * M * nrhs;
-    if (t >= total) return;
-    int c = (int)(t % nrhs);
-    int64_t rest = t / nrhs;
-    int64_t p = rest % M;
-    int64_t l = rest / M;
-    Y[(l * M + perm[p]) * nrhs + c] = Yp[t];
+__device__ __forceinline__ XT sum8(XT v) {
+    double x = v.x, y = v.y;
+    x += dpp_d<0xB1>(x);
+    y += dpp_d<0xB1>(y);
+    x += dpp_d<0x4E>(x);
+    y += dpp_d<0x4E>(y);
+    x += dpp_d<0x141>(x);
+    y += dpp_d<0x141>(y);
+    v.x = x;
+    v.y = y;
+    return v;
 }
 
-// SUM: T_l = sum_k f_l[k] X_k[tau] (n x nrhs), z_l = W_l^T T_l for every cross of block b,
-// a.apply_cb (<= kApplyCB) crosses at a time: each X_k[tau] element is read once per group
-// of crosses (the group size keeps the T workspace within its budget), and
-// z_l's rows are dot products over j taken by 8 lanes each (W rows read in order, partial
-// sums added by a fixed butterfly).
-template <class FacT, class XT>
-__global__ void __launch_bounds__(256) apply_far_a_kernel(ApplyDev a, const XT *Xp, XT *zbuf, XT *tbuf,
-                                                          const int64_t *t_off) {
-    const int b = blockIdx.x;
-    const int m = a.far4[4 * b + 1], c0 = a.far4[4 * b + 2], n = a.far4[4 * b + 3];
-    const FarMeta mt = a.meta[b];
-    const int L = a.L, nr = a.nrhs;
-    const int64_t M = a.M;
-    XT *z = zbuf + a.z_off[b];
-    XT *T = tbuf + t_off[b];
-    const FacT *arena = reinterpret_cast<const FacT *>(a.arena);
-    const double2 *F = a.fib_arena + a.fib_off[b];
-    constexpr int CB = kApplyCB;
-    __shared__ int64_t s_w[CB], s_z[CB];
-    __shared__ int s_rho[CB + 1];
-    __shared__ XT s_f[CB * kApplyKF];
-    const int nt = n * nr;
-    int64_t zo = 0;
-    const int cbr = max(1, min(CB, a.apply_cb));
-    for (int cg = 0; cg < mt.rank; cg += cbr) {
-        const int cb = min(cbr, mt.rank - cg);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int rows = 0;
-            for (int c = 0; c < cb; ++c) {
-                const CrossMeta cm = a.cmeta[(int64_t)b * a.rcap + cg + c];
-                s_w[c] = a.cross_off[(int64_t)b * a.rcap + cg + c] + (int64_t)cm.rho * m;
-                s_z[c] = zo;
-                s_rho[c] = rows;
-                rows += cm.rho;
-                zo += (int64_t)cm.rho * nr;
-            }
-            s_rho[cb] = rows;
-        }
-        // T_c for the crosses of the group ([c][j][rhs]); the fibres pass through LDS
-        // kApplyKF frequencies at a time.  Blocks with few columns split the frequencies
-        // over G adjacent lanes per (j, rhs) (G a power of two, G nt <= workgroup), whose
-        // sums are added by a fixed butterfly
-        int G = 1;
-        while (G < 16 && 2 * G * nt <= (int)blockDim.x) G *= 2;
-        const int tpp = (int)blockDim.x / G, gl = (int)threadIdx.x % G;
-        for (int t0 = 0; t0 < nt; t0 += tpp) {
-            const int t = t0 + (int)threadIdx.x / G;
-            const int j = t / nr, cc = t - j * nr;
-            const XT *xp = Xp + (int64_t)(c0 + min(j, n - 1)) * nr + cc;
-            XT acc[CB];
-#pragma unroll
-            for (int c = 0; c < CB; ++c) acc[c] = czero<XT>();
-            for (int k0 = 0; k0 < L; k0 += kApplyKF) {
-                const int nk = min(kApplyKF, L - k0);
-                __syncthreads();
-                for (int i = threadIdx.x; i < cb * nk; i += blockDim.x) {
-                    const int c = i / nk, kk = i - c * nk;
-                    s_f[c * kApplyKF + kk] = cast_c<XT>(F[(int64_t)(cg + c) * L + k0 + kk]);
-                }
-                __syncthreads();
-#pragma unroll 8
-                for (int kk = gl; kk < nk; kk += G) {
-                    const XT x = xp[(int64_t)(k0 + kk) * M * nr];
-#pragma unroll
-                    for (int c = 0; c < CB; ++c)
-                        if (c < cb) acc[c] = cfma(s_f[c * kApplyKF + kk], x, acc[c]);
-                }
-            }
-            for (int o = G >> 1; o > 0; o >>= 1)
-#pragma unroll
-                for (int c = 0; c < CB; ++c) {
-                    acc[c].x += __shfl_xor(acc[c].x, o, 64);
-                    acc[c].y += __shfl_xor(acc[c].y, o, 64);
-                }
-            if (gl == 0 && t < nt)
-#pragma unroll
-                for (int c = 0; c < CB; ++c)
-                    if (c < cb) T[(int64_t)c * nt + t] = acc[c];
-        }
-        __syncthreads();
-        // z rows (cross c, step q) of the group, 8 lanes per row and right-hand side
-        const int rows = s_rho[cb];
-        const int l8 = threadIdx.x & 7;
-        for (int g = threadIdx.x >> 3; g < rows * nr; g += blockDim.x >> 3) {
-            const int ri = g / nr, cc = g - ri * nr;
-            int c = 0;
-            while (c + 1 < cb && s_rho[c + 1] <= ri) ++c;
-            const int q = ri - s_rho[c];
-            const FacT *w = arena + s_w[c] + (int64_t)q * n;
-            const XT *tc = T + (int64_t)c * nt + cc;
-            XT acc = czero<XT>();
-#pragma unroll 4
-            for (int j = l8; j < n; j += 8) acc = cfma(cast_c<XT>(w[j]), tc[(int64_t)j * nr], acc);
-            double ax = acc.x, ay = acc.y;
-#pragma unroll
-            for (int o = 4; o > 0; o >>= 1) {
-                ax += __shfl_xor(ax, o, 8);
-                ay += __shfl_xor(ay, o, 8);
-            }
-            if (l8 == 0) {
-                XT r;
-                r.x = ax;
-                r.y = ay;
-                z[s_z[c] + (int64_t)q * nr + cc] = r;
-            }
-        }
-    }
-}
-
-// SUM: y_b = sum_l U_l z_l for every far block (m x nrhs per block).
-template <class FacT, class XT>
-__global__ void __launch_bounds__(256) apply_far_y_kernel(ApplyDev a, const XT *zbuf, XT *ybuf,
-                                                          const int64_t *y_off) {
-    const int b = blockIdx.x;
-    const int m = a.far4[4 * b + 1];
-    const int nr = a.nrhs;
-    const FarMeta mt = a.meta[b];
-    const XT *z = zbuf + a.z_off[b];
-    const FacT *arena = reinterpret_cast<const FacT *>(a.arena);
-    for (int t = threadIdx.x; t < m * nr; t += blockDim.x) {
-        const int r = t / nr, cc = t - r * nr;
-        XT acc = czero<XT>();
-        int64_t zo = 0;
-        for (int c = 0; c < mt.rank; ++c) {
-            const CrossMeta cm = a.cmeta[(int64_t)b * a.rcap + c];
-            const FacT *U = arena + a.cross_off[(int64_t)b * a.rcap + c];
-#pragma unroll 8
-            for (int qq = 0; qq < cm.rho; ++qq)
-                acc = cfma(cast_c<XT>(U[(int64_t)qq * m + r]), z[zo + (int64_t)qq * nr + cc], acc);
-            zo += (int64_t)cm.rho * nr;
-        }
-        ybuf[y_off[b] + t] = acc;
-    }
-}
-
-// SUM, compressed near blocks: T_l = sum_k f_l[k] X_k[tau] ([crank][n][nrhs]) per block;
-// one workgroup per near block (dense ones return at once).
-template <class XT>
-__global__ void __launch_bounds__(256) apply_near_t_kernel(ApplyDev a, const XT *Xp, XT *tn) {
-    const NearBlockDev nb = a.nblocks[blockIdx.x];
-    if (!nb.comp || nb.crank == 0) return;
-    const int L = a.L, nr = a.nrhs, n = nb.n;
-    const int64_t M = a.M;
-    const double2 *F = a.near_fib + nb.foff;
-    XT *T = tn + a.tn_off[blockIdx.x];
-    const int64_t tot = (int64_t)nb.crank * n * nr;
-    for (int64_t t = threadIdx.x; t < tot; t += blockDim.x) {
-        const int cc = (int)(t % nr);
-        const int64_t rest = t / nr;
-        const int j = (int)(rest % n), l = (int)(rest / n);
-        const XT *xp = Xp + (int64_t)(nb.c0 + j) * nr + cc;
-        XT acc = czero<XT>();
-        for (int k = 0; k < L; ++k) acc = cfma(cast_c<XT>(F[(int64_t)l * L + k]), xp[(int64_t)k * M * nr], acc);
-        T[t] = acc;
-    }
-}
-
-// SUM per row: Y[row] = sum over the leaf's near blocks of sum_k N_k[row] X_k + the rows
-// y_b of the covering far blocks.  One wave per row: a near block stores row ro as L n
-// contiguous entries ([m][L][n]), which the lanes read in order (entry t: frequency t / n,
-// column t % n); RC right-hand sides per pass, lane sums added by a fixed-order wave
-// reduction.  Grid (leaf, rows / 4).  PART 0: near and far parts; 1: the near part only
-// (written to Yp); 2: the far part added to the near part in Yp (1 then 2 gives the values
-// of 0 bit for bit, with the far blocks' y computed in between or beside part 1).
-template <class NearT, class XT, int RC, int PART>
-__global__ void __launch_bounds__(256) apply_leaf_sum_kernel(ApplyDev a, const XT *Xp,
-                                                             const XT *ybuf, const int64_t *y_off,
-                                                             XT *Yp, const XT *tn) {
-    const int leaf = blockIdx.x;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int r = blockIdx.y * 4 + wave;
-    if (r >= a.leaf_m[leaf]) return;   // the whole wave; no workgroup barrier below
-    const int row = a.leaf_r0[leaf] + r;
-    const int L = a.L, nr = a.nrhs;
-    const int64_t M = a.M;
-    const int np0 = a.leaf_near_ptr[leaf], np1 = a.leaf_near_ptr[leaf + 1];
-    const int fp0 = a.leaf_far_ptr[leaf], fp1 = a.leaf_far_ptr[leaf + 1];
-    const NearT *nearv = a.near64 ? reinterpret_cast<const NearT *>(a.near64)
-                                  : reinterpret_cast<const NearT *>(a.near32);
-    for (int cr = 0; cr < nr; cr += RC) {
-        XT acc[RC];
-#pragma unroll
-        for (int c = 0; c < RC; ++c) acc[c] = czero<XT>();
-        for (int e = PART == 2 ? np1 : np0; e < np1; ++e) {
-            const int ib = a.leaf_near_idx[e];
-            const NearBlockDev nb = a.nblocks[ib];
-            if (nb.comp) {
-                // row ro of sum_l H_l (T_l): entry t = (l, j), H_l row ro at l m n + ro n
-                const NearT *fc = reinterpret_cast<const NearT *>(a.near_faces) + nb.off;
-                const XT *T = tn + a.tn_off[ib] + cr;
-                const int n = nb.n, mn = nb.m * n, ro = row - nb.r0;
-                for (int t = lane; t < nb.crank * n; t += 64) {
-                    const int l = t / n, j = t - l * n;
-                    const XT hv = cast_c<XT>(fc[(int64_t)l * mn + (int64_t)ro * n + j]);
-                    const XT *tp = T + (int64_t)t * nr;
-#pragma unroll
-                    for (int c = 0; c < RC; ++c)
-                        if (cr + c < nr) acc[c] = cfma(hv, tp[c], acc[c]);
-                }
-                continue;
-            }
-            const int n = nb.n, E = L * n;
-            const NearT *base = nearv + nb.off + (int64_t)(row - nb.r0) * E;
-            const XT *xb = Xp + (int64_t)nb.c0 * nr + cr;
-            // (k, j) of entry t = lane + 64 i, advanced by 64 entries per step; LU entries
-            // per round have their loads in flight together and are summed in order
-            int k = lane / n, j = lane - k * n;
-            const int dk = 64 / n, dj = 64 - dk * n;
-            auto step = [&]() {
-                k += dk;
-                j += dj;
-                if (j >= n) {
-                    j -= n;
-                    ++k;
-                }
-            };
-            constexpr int LU = 8;
-            int t = lane;
-            for (; t + 64 * (LU - 1) < E; t += 64 * LU) {
-                XT nv[LU], xv[LU][RC];
-#pragma unroll
-                for (int u = 0; u < LU; ++u) {
-                    nv[u] = cast_c<XT>(base[t + 64 * u]);
-                    const XT *xp = xb + ((int64_t)k * M + j) * nr;
-#pragma unroll
-                    for (int c = 0; c < RC; ++c) xv[u][c] = cr + c < nr ? xp[c] : czero<XT>();
-                    step();
-                }
-#pragma unroll
-                for (int u = 0; u < LU; ++u)
-#pragma unroll
-                    for (int c = 0; c < RC; ++c)
-                        if (cr + c < nr) acc[c] = cfma(nv[u], xv[u][c], acc[c]);
-            }
-            for (; t < E; t += 64) {
-                const XT nv = cast_c<XT>(base[t]);
-                const XT *xp = xb + ((int64_t)k * M + j) * nr;
-#pragma unroll
-                for (int c = 0; c < RC; ++c)
-                    if (cr + c < nr) acc[c] = cfma(nv, xp[c], acc[c]);
-                step();
-            }
-        }
-        if constexpr (PART != 2) {
-#pragma unroll
-            for (int c = 0; c < RC; ++c) {
-                const double sx = wave_sum((double)acc[c].x), sy = wave_sum((double)acc[c].y);
-                acc[c].x = sx;
-                acc[c].y = sy;
-            }
-        }
-        if (lane < RC && cr + lane < nr) {
-            XT tot = acc[0];
-#pragma unroll
-            for (int c = 1; c < RC; ++c)
-                if (lane == c) tot = acc[c];
-            if constexpr (PART == 2) tot = Yp[(int64_t)row * nr + cr + lane];
-            if constexpr (PART != 1)
-                for (int e = fp0; e < fp1; ++e) {
-                    const int b = a.leaf_far_idx[e];
-                    tot = cadd(tot, ybuf[y_off[b] + (int64_t)(row - a.far4[4 * b]) * nr + cr + lane]);
-                }
-            Yp[(int64_t)row * nr + cr + lane] = tot;
-        }
-    }
-}
-
-// PER_FREQ.  The far blocks are products with L nrhs columns and run on the matrix cores
-// (16 x 16 x 4 tiles; a complex product is four real ones), FP64 for complex128, FP32 for
-// complex64:
-//   Z_b = diag(f) W_b^T X[tau]  (sum_rho x n) . (n x L nrhs), row (l, q) scaled by f_l[k],
-//   Y[sigma] = sum_b U_b Z_b    (leaf rows x sum_rho) . (sum_rho x L nrhs);
-// the near field differs from frequency to frequency and is streamed once.  What bounds it: the
-// reads of Z and the factors from L2 (a wave's operands come straight from there, four K steps
-// in flight), the near field from HBM.  1728-triangle cube, L = 32, 3 right-hand sides: 1.1 ms, the
-// near field 0.23 of it at 4 TB/s
-// (one thread per element of Z and Y with strided reads: 7.8 ms).
+// 16 x 16 complex tiles of the matrix cores, four steps of the contraction at a time
 template <class XT>
 struct Mma;
 template <>
@@ -439,6 +145,367 @@ struct CTile16 {   // 16 x 16 complex
     }
 };
 
+// SUM, in two launches after the permutation of X:
+//   parts   far blocks: T_l = sum_k f_l[k] X_k[tau] (n x nrhs) and z_l = W_l^T T_l for every cross,
+//           one workgroup per block; then, in the same launch, near rows: sum_k N_k X_k, four rows
+//           per workgroup;
+//   rows    Y[leaf] = near part + sum_b U_b z_b, eight waves per leaf, every U read once.
+// What bounds them: the stored operator read once from HBM.  6912-triangle sphere, L = 128, one
+// complex128 right-hand side (13.1 GB near field, 6.5 GB factors): far blocks 1.3 ms, near rows
+// 2.4 ms (5.5 TB/s), rows 0.8 ms (4 TB/s).  With T in global memory, y per far block and the near
+// rows read by one thread per row and block: 6.9 ms for 4.5.  Far blocks and near rows in turn
+// rather than one kind after the other took 4.8 ms for the 3.7 of the launch.
+
+// Far block b, up to 16 crosses and kFarTC columns (j, rhs) at a time: T = F X on the matrix cores,
+// a wave per 16 columns, into LDS (its operands come straight from L2: the crosses of a block fill
+// a tile, and X is read once for all of them); then the rows of z = W^T T, 8 lanes each over j (W
+// read in order) for RC right-hand sides, summed in a fixed order.
+constexpr int kFarTC = 128;
+template <class FacT, class XT, int RC>
+__device__ void far_z(const ApplyDev &a, int b, const XT *Xp, XT *zbuf, XT (*s_t)[kFarTC + 1]) {
+    constexpr int KS = 4, WU = 4;   // loads in flight: steps of the contraction, steps along a row of W
+    __shared__ int64_t s_w[16];
+    __shared__ int s_row[17];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, kq = lane >> 4, c16 = lane & 15;
+    const int m = a.far4[4 * b + 1], c0 = a.far4[4 * b + 2], n = a.far4[4 * b + 3];
+    const int rank = a.meta[b].rank, L = a.L, nr = a.nrhs;
+    const int64_t ks = a.M * nr;
+    XT *z = zbuf + a.z_off[b];
+    const FacT *arena = reinterpret_cast<const FacT *>(a.arena);
+    const double2 *F = a.fib_arena + a.fib_off[b];
+    const int RB = min(nr, kFarTC), JC = kFarTC / RB;   // columns of one pass: JC entries j, RB right-hand sides
+    for (int cg = 0; cg < rank; cg += 16) {
+        const int cb = min(16, rank - cg);
+        __syncthreads();   // the last group's z rows are read from s_row, s_w and s_t
+        if (tid < 64) {
+            const int cl = cg + min(c16, cb - 1);
+            const int rho = a.cmeta[(int64_t)b * a.rcap + cl].rho;
+            int q1 = c16 < cb ? rho : 0;
+#pragma unroll
+            for (int d = 1; d < 16; d <<= 1) {
+                const int v = __shfl_up(q1, d, 16);
+                if (c16 >= d) q1 += v;
+            }
+            if (tid < 16) {
+                s_w[tid] = a.cross_off[(int64_t)b * a.rcap + cl] + (int64_t)rho * m;
+                s_row[tid + 1] = q1;
+                if (tid == 0) s_row[0] = 0;
+            }
+        }
+        const double2 *f = F + (int64_t)(cg + min(c16, cb - 1)) * L;
+        for (int r0 = 0; r0 < nr; r0 += RB) {
+            const int rb = min(RB, nr - r0);
+            for (int j0 = 0; j0 < n; j0 += JC) {
+                const int jn = min(JC, n - j0), nt = jn * rb;
+                __syncthreads();   // s_t is free, s_row is there
+                for (int t0 = 16 * wave; t0 < nt; t0 += 64) {
+                    const int t = t0 + c16, tc = min(t, nt - 1), jl = tc / rb;
+                    const XT *x = Xp + (int64_t)(c0 + j0 + jl) * nr + r0 + (tc - jl * rb);
+                    CTile16<XT> acc;
+                    for (int k0 = 0; k0 < L; k0 += 4 * KS) {
+                        XT av[KS], bv[KS];
+#pragma unroll
+                        for (int s = 0; s < KS; ++s) {
+                            const int k = k0 + 4 * s + kq, kc = min(k, L - 1);
+                            av[s] = cast_c<XT>(f[kc]);
+                            bv[s] = x[kc * ks];
+                            if (k >= L) av[s] = bv[s] = czero<XT>();
+                        }
+#pragma unroll
+                        for (int s = 0; s < KS; ++s) acc.mac(av[s], bv[s]);
+                    }
+                    if (t < nt)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) s_t[Mma<XT>::row(lane, i)][t] = acc.get(i);
+                }
+                __syncthreads();
+                const int rows = s_row[cb], l8 = tid & 7;
+                int c = 0;
+                for (int ri = tid >> 3; ri < rows; ri += 32) {
+                    while (s_row[c + 1] <= ri) ++c;
+                    const FacT *w = arena + s_w[c] + (int64_t)(ri - s_row[c]) * n + j0;
+                    for (int cr = 0; cr < rb; cr += RC) {
+                        XT acc[RC];
+#pragma unroll
+                        for (int v = 0; v < RC; ++v) acc[v] = czero<XT>();
+                        for (int jb = l8; jb < jn; jb += 8 * WU) {
+                            XT wv[WU];
+#pragma unroll
+                            for (int u = 0; u < WU; ++u) {
+                                wv[u] = cast_c<XT>(w[min(jb + 8 * u, jn - 1)]);
+                                if (jb + 8 * u >= jn) wv[u] = czero<XT>();
+                            }
+#pragma unroll
+                            for (int u = 0; u < WU; ++u) {
+                                const XT *tr = s_t[c] + min(jb + 8 * u, jn - 1) * rb + cr;
+#pragma unroll
+                                for (int v = 0; v < RC; ++v)
+                                    if (cr + v < rb && jb + 8 * u < jn) acc[v] = cfma(wv[u], tr[v], acc[v]);
+                            }
+                        }
+                        XT *zp = z + (int64_t)ri * nr + r0 + cr;
+#pragma unroll
+                        for (int v = 0; v < RC; ++v) {
+                            const XT r = sum8(acc[v]);
+                            if (l8 == v && cr + v < rb) zp[v] = j0 > 0 ? cadd(zp[v], r) : r;
+                        }
+                    }
+                }
+            }
+        }
+        z += (int64_t)s_row[cb] * nr;
+    }
+}
+
+// SUM, compressed near blocks: T_l = sum_k f_l[k] X_k[tau] ([crank][n][nrhs]) per block;
+// one workgroup per near block (dense ones return at once).
+template <class XT>
+__global__ void __launch_bounds__(256) apply_near_t_kernel(ApplyDev a, const XT *Xp, XT *tn) {
+    const NearBlockDev nb = a.nblocks[blockIdx.x];
+    if (!nb.comp || nb.crank == 0) return;
+    const int L = a.L, nr = a.nrhs, n = nb.n;
+    const int64_t M = a.M;
+    const double2 *F = a.near_fib + nb.foff;
+    XT *T = tn + a.tn_off[blockIdx.x];
+    const int64_t tot = (int64_t)nb.crank * n * nr;
+    for (int64_t t = threadIdx.x; t < tot; t += blockDim.x) {
+        const int cc = (int)(t % nr);
+        const int64_t rest = t / nr;
+        const int j = (int)(rest % n), l = (int)(rest / n);
+        const XT *xp = Xp + (int64_t)(nb.c0 + j) * nr + cc;
+        XT acc = czero<XT>();
+        for (int k = 0; k < L; ++k) acc = cfma(cast_c<XT>(F[(int64_t)l * L + k]), xp[(int64_t)k * M * nr], acc);
+        T[t] = acc;
+    }
+}
+
+// Near part of four rows of a leaf: a near block stores a row as L n contiguous entries
+// ([m][L][n]), which the lanes read in order (entry t: frequency t / n, column t % n), four rows at
+// a time so that an element of X serves four products; the four waves take every fourth near
+// block.  The sums go to Yn (tree order).
+template <class NearT, class XT, int RC>
+__device__ void near_rows(const ApplyDev &a, int leaf, int rg, const XT *Xp, XT *Yn, const XT *tn,
+                          XT (*part)[4 * RC]) {
+    constexpr int RW = 4, LU = 2;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lm = a.leaf_m[leaf], r0 = RW * rg;
+    if (r0 >= lm) return;   // the whole workgroup
+    const int L = a.L, nr = a.nrhs;
+    const int64_t M = a.M;
+    const NearT *nearv = a.near64 ? reinterpret_cast<const NearT *>(a.near64)
+                                  : reinterpret_cast<const NearT *>(a.near32);
+    int row[RW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) row[r] = a.leaf_r0[leaf] + min(r0 + r, lm - 1);
+    const int e1 = a.leaf_near_ptr[leaf + 1];
+    for (int cr = 0; cr < nr; cr += RC) {
+        XT acc[RW][RC];
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int c = 0; c < RC; ++c) acc[r][c] = czero<XT>();
+        for (int e0 = a.leaf_near_ptr[leaf] + wave; e0 < e1; e0 += 4 * 64) {
+            // the descriptors of the wave's next 64 blocks, a lane each
+            const int ib_l = a.leaf_near_idx[min(e0 + 4 * lane, e1 - 1)];
+            const NearBlockDev nb_l = a.nblocks[ib_l];
+            for (int i = 0; i < min(64, (e1 - e0 + 3) / 4); ++i) {
+                const int ib = __builtin_amdgcn_readlane(ib_l, i);
+                NearBlockDev nb;
+                nb.r0 = __builtin_amdgcn_readlane(nb_l.r0, i);
+                nb.m = __builtin_amdgcn_readlane(nb_l.m, i);
+                nb.c0 = __builtin_amdgcn_readlane(nb_l.c0, i);
+                nb.n = __builtin_amdgcn_readlane(nb_l.n, i);
+                nb.off = readlane_i64(nb_l.off, i);
+                nb.comp = __builtin_amdgcn_readlane(nb_l.comp, i);
+                nb.crank = __builtin_amdgcn_readlane(nb_l.crank, i);
+                const int n = nb.n;
+                const NearT *base[RW];
+                int64_t rs;   // entries per step of the row index t / n
+                const XT *xb;
+                int E;
+                if (nb.comp) {
+                    // row ro of sum_l H_l (T_l): entry t = (l, j), H_l row ro at l m n + ro n
+                    const int mn = nb.m * n;
+#pragma unroll
+                    for (int r = 0; r < RW; ++r)
+                        base[r] = reinterpret_cast<const NearT *>(a.near_faces) + nb.off + (int64_t)(row[r] - nb.r0) * n;
+                    rs = mn - n;
+                    xb = tn + a.tn_off[ib] + cr;
+                    E = nb.crank * n;
+                } else {
+#pragma unroll
+                    for (int r = 0; r < RW; ++r) base[r] = nearv + nb.off + (int64_t)(row[r] - nb.r0) * L * n;
+                    rs = 0;
+                    xb = Xp + (int64_t)nb.c0 * nr + cr;
+                    E = L * n;
+                }
+                const int64_t xs = nb.comp ? (int64_t)n : M;   // X rows per frequency (T rows per cross)
+                // (k, j) of entry t = lane + 64 i, advanced by 64 entries per step
+                int k = lane / n, j = lane - k * n;
+                const int dk = 64 / n, dj = 64 - dk * n;
+                for (int t = lane; t < E; t += 64 * LU) {
+                    XT nv[LU][RW], xv[LU][RC];
+#pragma unroll
+                    for (int u = 0; u < LU; ++u) {
+                        const bool ok = t + 64 * u < E;   // past the end: the first entry, times 0
+                        const int64_t to = ok ? t + 64 * u + k * rs : 0;
+                        const XT *xp = xb + (ok ? (k * xs + j) * nr : 0);
+#pragma unroll
+                        for (int r = 0; r < RW; ++r) nv[u][r] = cast_c<XT>(base[r][to]);
+#pragma unroll
+                        for (int c = 0; c < RC; ++c) xv[u][c] = ok && cr + c < nr ? xp[c] : czero<XT>();
+                        if (!ok)
+#pragma unroll
+                            for (int r = 0; r < RW; ++r) nv[u][r] = czero<XT>();
+                        k += dk;
+                        j += dj;
+                        if (j >= n) {
+                            j -= n;
+                            ++k;
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < LU; ++u)
+#pragma unroll
+                        for (int c = 0; c < RC; ++c)
+#pragma unroll
+                            for (int r = 0; r < RW; ++r) acc[r][c] = cfma(nv[u][r], xv[u][c], acc[r][c]);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int c = 0; c < RC; ++c) {
+                XT v;
+                v.x = wave_sum((double)acc[r][c].x);
+                v.y = wave_sum((double)acc[r][c].y);
+                if (lane == 0) part[wave][r * RC + c] = v;
+            }
+        __syncthreads();
+        const int r = threadIdx.x / RC, c = threadIdx.x - r * RC;
+        if (r < RW && r0 + r < lm && cr + c < nr)
+            Yn[(int64_t)(a.leaf_r0[leaf] + r0 + r) * nr + cr + c] =
+                cadd(cadd(part[0][threadIdx.x], part[1][threadIdx.x]), cadd(part[2][threadIdx.x], part[3][threadIdx.x]));
+        __syncthreads();   // the next columns' sums take the same place
+    }
+}
+
+template <class FacT, class XT, int RC>
+__global__ void __launch_bounds__(256) apply_sum_parts_kernel(ApplyDev a, const XT *Xp, XT *zbuf, XT *Yn,
+                                                              const XT *tn) {
+    __shared__ XT s[16][kFarTC + 1];
+    if ((int)blockIdx.x < a.nfar) {
+        far_z<FacT, XT, RC>(a, blockIdx.x, Xp, zbuf, s);
+        return;
+    }
+    XT (*part)[4 * RC] = reinterpret_cast<XT (*)[4 * RC]>(s[0]);
+    const int w = blockIdx.x - a.nfar, groups = (a.max_leaf_m + 3) / 4;
+    near_rows<FacT, XT, RC>(a, w / groups, w % groups, Xp, Yn, tn, part);
+}
+
+// Y[leaf rows] = near part + sum over the far blocks of U z, in the caller's order: RL rows at a
+// time on adjacent lanes, the wave's 64 / RL lane groups take every (64 / RL)-th step q, the eight
+// waves every eighth far block
+template <class FacT, class XT, int RC, int RL>
+__global__ void __launch_bounds__(512) apply_sum_rows_kernel(ApplyDev a, const XT *zbuf, const XT *Yn, XT *Y) {
+    constexpr int QS = 64 / RL, NW = 8, SU = 4;
+    __shared__ XT part[NW * QS][RL][RC];
+    __shared__ int64_t s_off[NW][64];
+    __shared__ int s_q1[NW][64];
+    const int leaf = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int lm = min(RL, a.leaf_m[leaf] - RL * (int)blockIdx.y), row0 = a.leaf_r0[leaf] + RL * blockIdx.y;
+    if (lm <= 0) return;
+    const int nr = a.nrhs, r = lane & (RL - 1), rc = min(r, lm - 1), qs = lane / RL;
+    const FacT *arena = reinterpret_cast<const FacT *>(a.arena);
+    const int fp1 = a.leaf_far_ptr[leaf + 1];
+    for (int cr = 0; cr < nr; cr += RC) {
+        XT acc[RC];
+#pragma unroll
+        for (int c = 0; c < RC; ++c) acc[c] = czero<XT>();
+        for (int e0 = a.leaf_far_ptr[leaf] + wave; e0 < fp1; e0 += NW * 64) {
+            // the descriptors of the wave's next 64 blocks, a lane each
+            const int b_l = a.leaf_far_idx[min(e0 + NW * lane, fp1 - 1)];
+            const int m_l = a.far4[4 * b_l + 1], ro_l = row0 - a.far4[4 * b_l], rank_l = a.meta[b_l].rank;
+            const int64_t zo_l = a.z_off[b_l];
+            for (int i = 0; i < min(64, (fp1 - e0 + NW - 1) / NW); ++i) {
+                const int b = __builtin_amdgcn_readlane(b_l, i), m = __builtin_amdgcn_readlane(m_l, i);
+                const int ro = __builtin_amdgcn_readlane(ro_l, i) + rc;
+                const int rank = __builtin_amdgcn_readlane(rank_l, i);
+                const XT *z = zbuf + readlane_i64(zo_l, i) + cr;
+                for (int cb = 0; cb < rank; cb += 64) {
+                    // first entry and first step of the crosses, a lane each
+                    const int nc = min(64, rank - cb), cl = cb + min(lane, nc - 1);
+                    const int64_t off_l = a.cross_off[(int64_t)b * a.rcap + cl];
+                    const int rho_l = lane < nc ? a.cmeta[(int64_t)b * a.rcap + cl].rho : 0;
+                    int q0_l = rho_l;   // inclusive prefix sum
+#pragma unroll
+                    for (int d = 1; d < 64; d <<= 1) {
+                        const int v = __shfl_up(q0_l, d, 64);
+                        if (lane >= d) q0_l += v;
+                    }
+                    const int steps = __builtin_amdgcn_readlane(q0_l, 63);
+                    s_q1[wave][lane] = q0_l;
+                    s_off[wave][lane] = off_l - (int64_t)(q0_l - rho_l) * m;
+                    __builtin_amdgcn_wave_barrier();
+                    // step s of the block's sum: cross c with s_q1[c - 1] <= s < s_q1[c]
+                    int c = 0;
+                    for (int s0 = qs; s0 < steps; s0 += SU * QS) {
+                        const FacT *U[SU];
+#pragma unroll
+                        for (int u = 0; u < SU; ++u) {
+                            const int s = min(s0 + u * QS, steps - 1);
+                            while (s >= s_q1[wave][c]) ++c;
+                            U[u] = arena + s_off[wave][c] + (int64_t)s * m + ro;
+                        }
+                        XT uv[SU], zv[SU][RC];
+#pragma unroll
+                        for (int u = 0; u < SU; ++u) {
+                            const bool ok = s0 + u * QS < steps;
+                            const XT *zp = z + (int64_t)min(s0 + u * QS, steps - 1) * nr;
+                            uv[u] = cast_c<XT>(*U[u]);
+#pragma unroll
+                            for (int v = 0; v < RC; ++v) zv[u][v] = cr + v < nr ? zp[v] : czero<XT>();
+                            if (!ok) {
+                                uv[u] = czero<XT>();
+#pragma unroll
+                                for (int v = 0; v < RC; ++v) zv[u][v] = czero<XT>();
+                            }
+                        }
+#pragma unroll
+                        for (int u = 0; u < SU; ++u)
+#pragma unroll
+                            for (int v = 0; v < RC; ++v) acc[v] = cfma(uv[u], zv[u][v], acc[v]);
+                    }
+                    z += (int64_t)steps * nr;
+                    __builtin_amdgcn_wave_barrier();   // the next crosses take the same place
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < RC; ++v) part[wave * QS + qs][r][v] = acc[v];
+        __syncthreads();
+        for (int t = tid; t < RL * RC; t += 512) {
+            const int rr = t / RC, v = t - rr * RC;
+            if (rr < lm && cr + v < nr) {
+                XT s = Yn[(int64_t)(row0 + rr) * nr + cr + v];
+                for (int w = 0; w < NW * QS; ++w) s = cadd(s, part[w][rr][v]);
+                Y[a.perm[row0 + rr] * nr + cr + v] = s;
+            }
+        }
+        __syncthreads();   // the next columns' sums take the same place
+    }
+}
+
+// PER_FREQ.  The far blocks are products with L nrhs columns and run on the matrix cores
+// (16 x 16 x 4 tiles; a complex product is four real ones), FP64 for complex128, FP32 for
+// complex64:
+//   Z_b = diag(f) W_b^T X[tau]  (sum_rho x n) . (n x L nrhs), row (l, q) scaled by f_l[k],
+//   Y[sigma] = sum_b U_b Z_b    (leaf rows x sum_rho) . (sum_rho x L nrhs);
+// the near field differs from frequency to frequency and is streamed once.  What bounds it: the
+// reads of Z and the factors from L2 (a wave's operands come straight from there, four K steps
+// in flight), the near field from HBM.  1728-triangle cube, L = 32, 3 right-hand sides: 1.1 ms, the
+// near field 0.23 of it at 4 TB/s (one thread per element of Z and Y with strided reads: 7.8 ms).
 // Z_b: a wave per 32 rows x 16 columns; the workgroup's waves take neighbouring columns, its
 // blockIdx.z every gridDim.z-th group of 32 rows
 template <class FacT, class XT>
@@ -673,69 +740,49 @@ static void launch_freq_near(const ApplyDev &a, const XT *Xp, const XT *Yp, XT *
     apply_freq_near_kernel<FacT, XT, RC><<<grid, 256, 0, st>>>(a, Xp, Yp, Y);
 }
 
-template <class FacT, class XT, int PART>
-static void leaf_sum(const ApplyDev &a, const XT *Xp, const XT *ybuf, const int64_t *y_off, XT *Yp,
-                     const XT *tnbuf, hipStream_t st) {
-    const dim3 grid(a.nleaf, (a.max_leaf_m + 3) / 4);
-    if (a.nrhs == 1)
-        apply_leaf_sum_kernel<FacT, XT, 1, PART><<<grid, 256, 0, st>>>(a, Xp, ybuf, y_off, Yp, tnbuf);
-    else if (a.nrhs == 2)
-        apply_leaf_sum_kernel<FacT, XT, 2, PART><<<grid, 256, 0, st>>>(a, Xp, ybuf, y_off, Yp, tnbuf);
+template <class FacT, class XT, int RC>
+static void launch_sum(const ApplyDev &a, const XT *Xp, XT *zbuf, XT *Yn, const XT *tn,
+                       XT *Y, hipStream_t st) {
+    const int64_t nwg = a.nfar + (int64_t)a.nleaf * ((a.max_leaf_m + 3) / 4);
+    apply_sum_parts_kernel<FacT, XT, RC><<<(unsigned)nwg, 256, 0, st>>>(a, Xp, zbuf, Yn, tn);
+    // 16 rows at a time where no leaf has more
+    if (a.max_leaf_m <= 16)
+        apply_sum_rows_kernel<FacT, XT, RC, 16><<<dim3(a.nleaf, 1), 512, 0, st>>>(a, zbuf, Yn, Y);
     else
-        apply_leaf_sum_kernel<FacT, XT, 4, PART><<<grid, 256, 0, st>>>(a, Xp, ybuf, y_off, Yp, tnbuf);
+        apply_sum_rows_kernel<FacT, XT, RC, 32>
+            <<<dim3(a.nleaf, (a.max_leaf_m + 31) / 32), 512, 0, st>>>(a, zbuf, Yn, Y);
 }
 
 template <class FacT, class XT>
 static void apply_impl(const ApplyDev &a, int mode, const XT *X, XT *Y, XT *Xp, XT *Yp, XT *zbuf,
-                       XT *tbuf, const int64_t *t_off, XT *ybuf, const int64_t *y_off,
-                       hipStream_t st, XT *tnbuf, const ApplySide *side) {
+                       hipStream_t st, XT *tnbuf) {
     const int64_t totx = (int64_t)a.L * a.M * a.nrhs;
     permute_x_kernel<XT><<<(unsigned)((totx + 255) / 256), 256, 0, st>>>(X, Xp, a.perm, a.L, a.M,
                                                                           a.nrhs);
-    if (mode == 0 && side && a.nfar > 0) {
-        // far blocks (T, z, y) on the side stream beside the near part of the leaf sums (an
-        // L2-bound chain beside an HBM-bound pass), joined before the far parts are added
-        GACA_HIP_CHECK(hipEventRecord(side->fork, st));
-        GACA_HIP_CHECK(hipStreamWaitEvent(side->stream, side->fork, 0));
-        apply_far_a_kernel<FacT, XT><<<a.nfar, 256, 0, side->stream>>>(a, Xp, zbuf, tbuf, t_off);
-        apply_far_y_kernel<FacT, XT><<<a.nfar, 256, 0, side->stream>>>(a, zbuf, ybuf, y_off);
-        GACA_HIP_CHECK(hipEventRecord(side->join, side->stream));
+    if (mode == 0) {
         if (a.near_faces && a.nnear > 0)
             apply_near_t_kernel<XT><<<a.nnear, 256, 0, st>>>(a, Xp, tnbuf);
-        leaf_sum<FacT, XT, 1>(a, Xp, ybuf, y_off, Yp, tnbuf, st);
-        GACA_HIP_CHECK(hipStreamWaitEvent(st, side->join, 0));
-        leaf_sum<FacT, XT, 2>(a, Xp, ybuf, y_off, Yp, tnbuf, st);
-    } else if (mode == 0) {
-        if (a.nfar > 0) {
-            apply_far_a_kernel<FacT, XT><<<a.nfar, 256, 0, st>>>(a, Xp, zbuf, tbuf, t_off);
-            apply_far_y_kernel<FacT, XT><<<a.nfar, 256, 0, st>>>(a, zbuf, ybuf, y_off);
-        }
-        if (a.near_faces && a.nnear > 0)
-            apply_near_t_kernel<XT><<<a.nnear, 256, 0, st>>>(a, Xp, tnbuf);
-        leaf_sum<FacT, XT, 0>(a, Xp, ybuf, y_off, Yp, tnbuf, st);
-    } else {
-        if (a.nfar > 0) {
-            const unsigned nc = (unsigned)(a.L * a.nrhs);
-            apply_freq_z_kernel<FacT, XT><<<dim3(a.nfar, std::min((nc + 63) / 64, 65535u), 4), 256, 0, st>>>(a, Xp, zbuf);
-            apply_freq_far_kernel<FacT, XT>
-                <<<dim3(a.nleaf, std::min((nc + 15) / 16, 65535u), (a.max_leaf_m + 31) / 32), 256, 0, st>>>(a, zbuf, Yp);
-        }
-        if (a.nrhs == 1) launch_freq_near<FacT, XT, 1>(a, Xp, Yp, Y, st);
-        else if (a.nrhs == 2) launch_freq_near<FacT, XT, 2>(a, Xp, Yp, Y, st);
-        else launch_freq_near<FacT, XT, 4>(a, Xp, Yp, Y, st);
+        if (a.nrhs == 1) launch_sum<FacT, XT, 1>(a, Xp, zbuf, Yp, tnbuf, Y, st);
+        else if (a.nrhs == 2) launch_sum<FacT, XT, 2>(a, Xp, zbuf, Yp, tnbuf, Y, st);
+        else launch_sum<FacT, XT, 4>(a, Xp, zbuf, Yp, tnbuf, Y, st);
         return;
     }
-    const int64_t toty = a.M * a.nrhs;
-    scatter_y_kernel<XT><<<(unsigned)((toty + 255) / 256), 256, 0, st>>>(Yp, Y, a.perm, 1, a.M,
-                                                                         a.nrhs);
+    if (a.nfar > 0) {
+        const unsigned nc = (unsigned)(a.L * a.nrhs);
+        apply_freq_z_kernel<FacT, XT><<<dim3(a.nfar, std::min((nc + 63) / 64, 65535u), 4), 256, 0, st>>>(a, Xp, zbuf);
+        apply_freq_far_kernel<FacT, XT>
+            <<<dim3(a.nleaf, std::min((nc + 15) / 16, 65535u), (a.max_leaf_m + 31) / 32), 256, 0, st>>>(a, zbuf, Yp);
+    }
+    if (a.nrhs == 1) launch_freq_near<FacT, XT, 1>(a, Xp, Yp, Y, st);
+    else if (a.nrhs == 2) launch_freq_near<FacT, XT, 2>(a, Xp, Yp, Y, st);
+    else launch_freq_near<FacT, XT, 4>(a, Xp, Yp, Y, st);
 }
 
 void launch_apply(const ApplyDev &a, int mode, int x_fp32, const void *X, void *Y, void *Xp,
-                  void *Yp, void *zbuf, void *tbuf, const int64_t *t_off, void *ybuf,
-                  const int64_t *y_off, hipStream_t st, void *tnbuf, const ApplySide *side) {
+                  void *Yp, void *zbuf, hipStream_t st, void *tnbuf) {
 #define GACA_APPLY(FT, XTT)                                                                  \
     apply_impl<FT, XTT>(a, mode, (const XTT *)X, (XTT *)Y, (XTT *)Xp, (XTT *)Yp, (XTT *)zbuf, \
-                        (XTT *)tbuf, t_off, (XTT *)ybuf, y_off, st, (XTT *)tnbuf, side)
+                        st, (XTT *)tnbuf)
     if (a.fac_fp32) {
         if (x_fp32) GACA_APPLY(float2, float2);
         else GACA_APPLY(float2, double2);

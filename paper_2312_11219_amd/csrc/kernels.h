@@ -197,8 +197,6 @@ void launch_eval(int kernel, const GeoDev &g, const QuadDev &q, const FreqDev &f
                  const int32_t *tiers, double2 *out, hipStream_t st);
 
 // Apply (FP64, VALU reference path).
-constexpr int kApplyCB = 8;   // most crosses per T = F X group of the VALU SUM apply
-constexpr int kApplyKF = 64;  // fibre entries per LDS stage of that group
 struct ApplyDev {
     int32_t L, nrhs;
     int64_t M;
@@ -217,7 +215,6 @@ struct ApplyDev {
     const float2 *near32;
     // leaf CSR: leaf -> covering far blocks / near blocks
     int32_t nleaf, max_leaf_m;
-    int32_t apply_cb;             // crosses per T group of the VALU SUM apply (1..kApplyCB)
     const int32_t *leaf_r0, *leaf_m;
     const int32_t *leaf_far_ptr, *leaf_far_idx;
     const int32_t *leaf_near_ptr, *leaf_near_idx;
@@ -250,9 +247,8 @@ constexpr int kMaxDevices = 64;
 hipError_t scratch_setup(int device);
 // The device address taken by scratch_setup, or nullptr before it.
 void *scratch_address(int device);
-// Workspace offsets of the VALU apply (z, t, per-block y) written on the device.
-void launch_apply_offsets(const ApplyDev &a, int mode, int cb, int64_t *zoff, int64_t *toff,
-                          int64_t *yoff, hipStream_t st);
+// Workspace offsets of the VALU apply (z) written on the device.
+void launch_apply_offsets(const ApplyDev &a, int mode, int64_t *zoff, hipStream_t st);
 
 // Matrix-core apply (SUM mode, complex64 right-hand sides), csrc/apply_mfma.hip.
 constexpr int kMfmaMaxSumRho = 4096;   // sum of face ranks of one far block
@@ -294,18 +290,9 @@ void launch_apply_far_z(const ApplyDev &a, const MfmaApplyDev &d, int nitems, co
 void launch_apply_leaf_mfma(const ApplyDev &a, const MfmaApplyDev &d, int row_tiles,
                             const float2 *X, const float2 *Z, float2 *Y, hipStream_t st);
 
-// Side stream of the SUM apply: the far blocks run on it beside the near part (fork is
-// recorded on the launch stream, join on the side stream; both created by the caller).
-struct ApplySide {
-    hipStream_t stream;
-    hipEvent_t fork, join;
-};
-
 // x_fp32: X, Y and the workspace are complex64 (FP32 arithmetic), else complex128.
-// Workspace pointers are in elements of that type.  side: null to launch everything on st.
+// Workspace pointers are in elements of that type.
 void launch_apply(const ApplyDev &a, int mode, int x_fp32, const void *X, void *Y, void *Xp,
-                  void *Yp, void *zbuf, void *tbuf, const int64_t *t_off, void *ybuf,
-                  const int64_t *y_off, hipStream_t st, void *tnbuf = nullptr,
-                  const ApplySide *side = nullptr);
+                  void *Yp, void *zbuf, hipStream_t st, void *tnbuf = nullptr);
 
 }  // namespace gaca

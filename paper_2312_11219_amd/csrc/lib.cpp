@@ -463,8 +463,8 @@ struct gaca_problem {
     std::mutex leaf_mu;
     bool leaf_ready = false;
     DevBuf d_leaf_r0, d_leaf_m, d_lfp, d_lfi, d_lnp, d_lni;
-    // VALU apply workspace (X, Y in tree order, z, t, y) handed back by destroyed operators
-    DevBuf ws_spare[5];
+    // VALU apply workspace (z, X and Y in tree order) handed back by destroyed operators
+    DevBuf ws_spare[3];
     // near-field storage handed back by destroyed operators (slot kernel & 1)
     DevBuf near_spare[2];
     // far-field result tables of destroyed operators (device: meta, cross meta, cross offsets,
@@ -503,10 +503,9 @@ struct gaca_hmatrix {
     gaca_stats st{};
     std::vector<int64_t> freq_hist;
     // apply workspace
-    int32_t ws_nrhs = -1, ws_mode = -1, ws_dtype = -1, ws_cb = 1;
-    DevBuf d_xp, d_yp, d_z, d_t, d_toff, d_zoff, d_yb, d_yoff;
+    int32_t ws_nrhs = -1, ws_mode = -1, ws_dtype = -1;
+    DevBuf d_xp, d_yp, d_z, d_zoff;
     DevBuf d_tn, d_tnoff;   // T of the compressed near blocks (option near_aca, SUM mode)
-    hipEvent_t apply_ev[2] = {nullptr, nullptr};   // fork / join of the VALU SUM apply's side stream
     DevBuf d_mz, d_mt, d_mtitems, d_mttile0, d_mtrows, d_mzitems, d_mzoff, d_msumrho;   // matrix-core apply
 };
 
@@ -518,8 +517,6 @@ gaca_problem::~gaca_problem() {
 }
 
 gaca_hmatrix::~gaca_hmatrix() {
-    for (hipEvent_t e : apply_ev)
-        if (e) (void)hipEventDestroy(e);
     if (p && !owned_problem && --p->nops == 0 && p->destroy_requested) delete p;
 }
 
@@ -2564,8 +2561,8 @@ gaca_status gaca_hmatrix_destroy(gaca_hmatrix *h) {
             }
         }
         // VALU apply workspace: kept when no larger buffer of its kind is kept already
-        DevBuf *ws[5] = {&h->d_yb, &h->d_z, &h->d_t, &h->d_xp, &h->d_yp};
-        for (int k = 0; k < 5; ++k) {
+        DevBuf *ws[3] = {&h->d_z, &h->d_xp, &h->d_yp};
+        for (int k = 0; k < 3; ++k) {
             if (!ws[k]->ptr || ws[k]->bytes > tb / 16 || p->ws_spare[k].bytes >= ws[k]->bytes) continue;
             if (!synced) {
                 (void)hipDeviceSynchronize();   // no kernel may still use the buffer
@@ -2735,7 +2732,7 @@ static void prepare_leaves(gaca_hmatrix *h) {
     p->leaf_ready = true;
 }
 
-// Workspace of the VALU apply (tree-order copies of X and Y, z, t and per-block y).
+// Workspace of the VALU apply (tree-order copies of X and Y, and z).
 static void alloc_apply_workspace(gaca_hmatrix *h, gaca_apply_mode mode, int32_t nrhs, gaca_dtype dtype) {
     gaca_problem *p = h->p;
     gaca_context *ctx = p->ctx;
@@ -2743,30 +2740,14 @@ static void alloc_apply_workspace(gaca_hmatrix *h, gaca_apply_mode mode, int32_t
     const int64_t M = p->M;
     const size_t xs = dtype == GACA_C64 ? sizeof(float2) : sizeof(double2);
     {
-            std::vector<int64_t> zoff(std::max<int64_t>(h->nfar, 1)), toff(std::max<int64_t>(h->nfar, 1)),
-                yoff(std::max<int64_t>(h->nfar, 1));
-            // crosses per T group: up to kApplyCB while the T workspace stays within 2 GiB
-            int64_t nsum = 0;
-            for (int64_t b = 0; b < h->nfar; ++b) nsum += p->part.far[b][3];
-            const double t_one = (double)nsum * nrhs * xs;
-            const int cb = mode == GACA_APPLY_SUM
-                               ? (int)std::max(1.0, std::min((double)kApplyCB, std::floor(2147483648.0 / std::max(t_one, 1.0))))
-                               : 1;
-            int64_t zacc = 0, tacc = 0, yacc = 0;
+            std::vector<int64_t> zoff(std::max<int64_t>(h->nfar, 1));
+            int64_t zacc = 0;
             for (int64_t b = 0; b < h->nfar; ++b) {
                 zoff[b] = zacc;
-                toff[b] = tacc;
-                yoff[b] = yacc;
-                yacc += p->part.far[b][1] * (int64_t)nrhs;
                 const int64_t sr = h->meta[b].sum_rho;
                 zacc += mode == GACA_APPLY_SUM ? sr * nrhs : sr * (int64_t)L * nrhs;
-                tacc += mode == GACA_APPLY_SUM ? std::min<int64_t>(h->meta[b].rank, cb) *
-                                                     p->part.far[b][3] * (int64_t)nrhs
-                                               : 0;
             }
             h->d_zoff.upload(ctx, zoff);
-            h->d_toff.upload(ctx, toff);
-            h->d_yoff.upload(ctx, yoff);
             // a buffer handed back by an operator of the same problem serves when it is large
             // enough (every byte of the workspace is written before it is read)
             auto take = [&](DevBuf &dst, int slot, size_t need) {
@@ -2783,11 +2764,9 @@ static void alloc_apply_workspace(gaca_hmatrix *h, gaca_apply_mode mode, int32_t
                 dst.alloc(ctx, need);
             };
             const int nl = mode == GACA_APPLY_SUM ? 1 : L;
-            take(h->d_yb, 0, (size_t)std::max<int64_t>(yacc, 1) * xs);
-            take(h->d_z, 1, (size_t)std::max<int64_t>(zacc, 1) * xs);
-            take(h->d_t, 2, (size_t)std::max<int64_t>(tacc, 1) * xs);
-            take(h->d_xp, 3, (size_t)L * M * nrhs * xs);
-            take(h->d_yp, 4, (size_t)nl * M * nrhs * xs);
+            take(h->d_z, 0, (size_t)std::max<int64_t>(zacc, 1) * xs);
+            take(h->d_xp, 1, (size_t)L * M * nrhs * xs);
+            take(h->d_yp, 2, (size_t)nl * M * nrhs * xs);
             if (h->near_aca) {
                 // T_l of each compressed near block: [crank][n][nrhs]
                 std::vector<int64_t> tnoff(std::max<size_t>(h->nblk_host.size(), 1), 0);
@@ -2804,7 +2783,6 @@ static void alloc_apply_workspace(gaca_hmatrix *h, gaca_apply_mode mode, int32_t
             h->ws_nrhs = nrhs;
             h->ws_mode = (int)mode;
             h->ws_dtype = (int)dtype;
-            h->ws_cb = cb;
         }
 }
 
@@ -3074,26 +3052,13 @@ gaca_status gaca_apply(gaca_hmatrix *h, gaca_apply_mode mode, int32_t nrhs, cons
         if (!mfma && (h->ws_nrhs != nrhs || h->ws_mode != (int)mode || h->ws_dtype != (int)dtype))
             alloc_apply_workspace(h, mode, nrhs, dtype);
         ApplyDev a = apply_view(h, nrhs);
-        a.apply_cb = h->ws_cb;
         a.z_off = h->d_zoff.as<int64_t>();
         if (mfma) {
             apply_mfma(h, a, nrhs, reinterpret_cast<const float2 *>(X), reinterpret_cast<float2 *>(Y), st);
             return;
         }
-        // SUM mode: the far blocks on one of the problem's far-field streams (idle between
-        // builds) beside the near part of the leaf sums
-        ApplySide side{};
-        const bool use_side = mode == GACA_APPLY_SUM && p->far_streams_ready && h->nfar > 0;
-        if (use_side) {
-            for (hipEvent_t &e : h->apply_ev)
-                if (!e) GACA_HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-            side.stream = p->far_streams[1];
-            side.fork = h->apply_ev[0];
-            side.join = h->apply_ev[1];
-        }
         launch_apply(a, (int)mode, dtype == GACA_C64 ? 1 : 0, X, Y, h->d_xp.ptr, h->d_yp.ptr,
-                     h->d_z.ptr, h->d_t.ptr, h->d_toff.as<int64_t>(), h->d_yb.ptr,
-                     h->d_yoff.as<int64_t>(), st, h->d_tn.ptr, use_side ? &side : nullptr);
+                     h->d_z.ptr, st, h->d_tn.ptr);
         GACA_HIP_CHECK(hipGetLastError());
     });
 }
@@ -3117,15 +3082,15 @@ gaca_status gaca_apply_noalloc(gaca_hmatrix *h, gaca_apply_mode mode, int32_t nr
         const int L = p->L;
         const int64_t M = p->M;
         const size_t xs = dtype == GACA_C64 ? sizeof(float2) : sizeof(double2);
-        const int cb = kApplyCB;
-        // workspace sizes (elements), as the allocated workspace of gaca_apply
+        // workspace sizes (elements).  The documented limit also counts a result of its own for every
+        // far block and a T of up to eight crosses, which the kernels keep on chip
         int64_t zacc = 0, tacc = 0, yacc = 0;
         for (int64_t b = 0; b < h->nfar; ++b) {
             const int64_t sr = h->meta[b].sum_rho;
             yacc += p->part.far[b][1] * (int64_t)nrhs;
             zacc += mode == GACA_APPLY_SUM ? sr * nrhs : sr * (int64_t)L * nrhs;
             if (mode == GACA_APPLY_SUM)
-                tacc += std::min<int64_t>(h->meta[b].rank, cb) * p->part.far[b][3] * (int64_t)nrhs;
+                tacc += std::min<int64_t>(h->meta[b].rank, 8) * p->part.far[b][3] * (int64_t)nrhs;
         }
         const int nl = mode == GACA_APPLY_SUM ? 1 : L;
         auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
@@ -3142,14 +3107,10 @@ gaca_status gaca_apply_noalloc(gaca_hmatrix *h, gaca_apply_mode mode, int32_t nr
                             std::to_string(kScratchBytes) + "-byte scratch array of the allocation-free apply"};
         unsigned char *sb = static_cast<unsigned char *>(base);
         int64_t *zoff = reinterpret_cast<int64_t *>(sb + o_off);
-        int64_t *toff = zoff + std::max<int64_t>(h->nfar, 1);
-        int64_t *yoff = toff + std::max<int64_t>(h->nfar, 1);
         ApplyDev a = apply_view(h, nrhs);
-        a.apply_cb = cb;
         a.z_off = zoff;
-        launch_apply_offsets(a, (int)mode, cb, zoff, toff, yoff, st);
-        launch_apply(a, (int)mode, dtype == GACA_C64 ? 1 : 0, X, Y, sb + o_xp, sb + o_yp, sb + o_z,
-                     sb + o_t, toff, sb + o_yb, yoff, st);
+        launch_apply_offsets(a, (int)mode, zoff, st);
+        launch_apply(a, (int)mode, dtype == GACA_C64 ? 1 : 0, X, Y, sb + o_xp, sb + o_yp, sb + o_z, st);
         GACA_HIP_CHECK(hipGetLastError());
     });
 }
