@@ -79,6 +79,14 @@ struct FreqDev {
     const double *re, *im;
 };
 
+// Power series of the near field in the frequency: the frequencies lie in |s - c| <= R, c real;
+// K terms (0: none, every pair is evaluated at every frequency)
+struct NearSeries {
+    double c, R;
+    int K;
+};
+constexpr double kNearSeriesMax = 6.0;   // largest R delta (touching pairs: max(|c|, R) rho)
+
 enum Tier : int32_t { TIER_FAR6 = 0, TIER_MID4 = 1, TIER_NEAR8 = 2, TIER_SELF = 3 };
 
 // One admissible block of a far-field batch (constant during the build).

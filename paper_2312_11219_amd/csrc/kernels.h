@@ -45,7 +45,7 @@ void launch_near_aca_expand(const NearBlockDev &D, int L, const void *face_arena
 
 // P1 double layer near field (every pair, all frequencies, FP64, stored as double2) and its
 // entry test hook (far[p] != 0: 6-point rule on every triangle).
-void launch_near_p1(const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearPair *pairs,
+void launch_near_p1(const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S, const NearPair *pairs,
                     int64_t npairs, const NearBlockDev *blocks, double2 *out64, hipStream_t st);
 void launch_eval_p1(const GeoDev &g, const QuadDev &q, const FreqDev &f, int64_t n,
                     const int32_t *rows, const int32_t *cols, const int32_t *ks,
@@ -80,12 +80,24 @@ void launch_near_gp1_pairs(int op, const GeoDev &g, const QuadDev &q, const Freq
 
 // Near field: every pair of one tier, all frequencies, FP64 compute, stored as double2
 // (out64) or float2 (out32).
-void launch_near(int kernel, int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f,
+// Near field from moments of the quadrature points (S.K > 0): the pairs within the series' bound.
+// launch_near, launch_near_galerkin and launch_near_p1 with the same S take the others.
+void launch_near_series(int kernel, int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
+                        const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks, double2 *out64,
+                        float2 *out32, hipStream_t st);
+void launch_near_series_galerkin(int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
+                                 const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks, double2 *out64,
+                                 float2 *out32, hipStream_t st);
+void launch_near_series_p1(const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
+                           const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks, double2 *out64,
+                           hipStream_t st);
+
+void launch_near(int kernel, int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
                  const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks,
                  double2 *out64, float2 *out32, hipStream_t st);
 
 // Galerkin single layer near field, one pair class (GalTier) per launch.
-void launch_near_galerkin(int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f,
+void launch_near_galerkin(int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
                           const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks,
                           double2 *out64, float2 *out32, hipStream_t st);
 

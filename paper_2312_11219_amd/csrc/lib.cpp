@@ -431,6 +431,9 @@ struct gaca_problem {
     int32_t L = 0;
     std::vector<double> s_re, s_im;
     bool mirror = false;
+    // near field as a power series in the frequency: disc of the frequencies, longest edge, diameter
+    NearSeries series{0.0, 0.0, 0};
+    double near_h = 0.0, near_diam = 0.0;
     int64_t M = 0;
     std::vector<int64_t> inv_perm;
     // device geometry / tables
@@ -1064,6 +1067,44 @@ static void upload_freq(gaca_problem *p) {
     p->f.L_eval = p->mirror ? (p->L + 1) / 2 : p->L;
 }
 
+// Disc of the frequencies and extents of the mesh for near_series.
+static void near_extents(gaca_problem *p) {
+    double lo = INFINITY, hi = -INFINITY;
+    for (int l = 0; l < p->L; ++l) {
+        lo = std::min(lo, p->s_re[l]);
+        hi = std::max(hi, p->s_re[l]);
+    }
+    NearSeries &S = p->series;
+    S = NearSeries{0.5 * (lo + hi), 0.0, 0};
+    for (int l = 0; l < p->L; ++l) S.R = std::max(S.R, std::hypot(p->s_re[l] - S.c, p->s_im[l]));
+    for (double h : p->mesh.hmax) p->near_h = std::max(p->near_h, h);
+    double a[3] = {INFINITY, INFINITY, INFINITY}, b[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (size_t v = 0; v < p->mesh.vert.size(); ++v) {
+        a[v % 3] = std::min(a[v % 3], p->mesh.vert[v]);
+        b[v % 3] = std::max(b[v % 3], p->mesh.vert[v]);
+    }
+    p->near_diam = std::hypot(b[0] - a[0], b[1] - a[1], b[2] - a[2]);
+}
+
+// Series of a near-field class: K = 0 if its pairs are evaluated at every frequency; rest: some may
+// be beyond the series' bound and are left to those kernels.
+static NearSeries near_series(const gaca_problem *p, int tier, bool &rest) {
+    NearSeries S = p->series;
+    // bound over the problem's pairs: a triangle lies within 2/3 of its longest edge of its
+    // centroid, a P1 patch within its longest edge of the vertex
+    const bool gal = p->scheme == GACA_GALERKIN_P0;
+    double z = S.R * p->near_h * (gal ? 4.0 / 3.0 : p->p1() ? 1.0 : 2.0 / 3.0);
+    if (gal && tier >= 3) z = std::max(std::fabs(S.c), S.R) * p->near_h * (tier == 5 ? 1.0 : 2.0);
+    const double zfar = (std::fabs(S.c) + S.R) * (p->near_diam + p->near_h) * (kNearSeriesMax / 600.0);
+    rest = !(std::max(z, zfar) <= kNearSeriesMax);
+    // With fewer than eight frequencies the moments cost more than the points; a disc far from
+    // the origin for its size needs powers of c / R
+    if (p->f.L_eval >= 8 && S.R >= 1e-3 * std::fabs(S.c) && std::isfinite(S.R))
+        S.K = z <= 2.0 ? 24 : z <= 3.5 ? 32 : 44;
+    if (S.K == 0) rest = true;
+    return S;
+}
+
 gaca_status gaca_problem_create(gaca_context *ctx, const double *xyz, int64_t nv,
                                 const int32_t *tri, int64_t M, const double *s_re,
                                 const double *s_im, int32_t L, gaca_scheme scheme,
@@ -1117,6 +1158,7 @@ gaca_status gaca_problem_create(gaca_context *ctx, const double *xyz, int64_t nv
         GACA_HIP_CHECK(hipSetDevice(ctx->device));
         upload_problem(p.get());
         upload_freq(p.get());
+        near_extents(p.get());
         if (scheme == GACA_GALERKIN_P1) upload_gp1_pairs(p.get());
         *out = p.release();
     });
@@ -2286,9 +2328,16 @@ static bool build_ops(gaca_problem *p, const std::vector<gaca_kernel> &kernels,
             GACA_HIP_CHECK(hipEventRecord(ev[1 + 2 * w], st));
             double2 *n64 = mixed ? nullptr : h->d_near.as<double2>();
             float2 *n32 = mixed ? h->d_near.as<float2>() : nullptr;
-            if (p->scheme == GACA_COLLOCATION_P1)
-                launch_near_p1(p->g, p->q, p->f, p->d_pairs[0].as<NearPair>(), p->npairs[0],
-                               p->d_nblocks.as<NearBlockDev>(), n64, st);
+            if (p->scheme == GACA_COLLOCATION_P1) {
+                bool rest;
+                const NearSeries S = near_series(p, 0, rest);
+                if (S.K > 0)
+                    launch_near_series_p1(p->g, p->q, p->f, S, p->d_pairs[0].as<NearPair>(), p->npairs[0],
+                                          p->d_nblocks.as<NearBlockDev>(), n64, st);
+                if (rest)
+                    launch_near_p1(p->g, p->q, p->f, S, p->d_pairs[0].as<NearPair>(), p->npairs[0],
+                                   p->d_nblocks.as<NearBlockDev>(), n64, st);
+            }
             if (p->scheme == GACA_GALERKIN_P1) {
                 const int op = kernels[w] == GACA_HYP ? 0 : 1;
                 if (p->gp1_nfc > 0 && !p->d_gp1_buf.ptr) {
@@ -2307,12 +2356,24 @@ static bool build_ops(gaca_problem *p, const std::vector<gaca_kernel> &kernels,
                                     p->d_nblocks.as<NearBlockDev>(), n64, st);
             }
             for (int t = 0; t < kNumTiers && !p->p1(); ++t) {
-                if (p->scheme == GACA_GALERKIN_P0)
-                    launch_near_galerkin(t, p->g, p->q, p->f, p->d_pairs[t].as<NearPair>(),
-                                         p->npairs[t], p->d_nblocks.as<NearBlockDev>(), n64, n32, st);
-                else if (t < 4)
-                    launch_near(kernels[w], t, p->g, p->q, p->f, p->d_pairs[t].as<NearPair>(),
-                                p->npairs[t], p->d_nblocks.as<NearBlockDev>(), n64, n32, st);
+                const bool gal = p->scheme == GACA_GALERKIN_P0;
+                const NearPair *pairs = p->d_pairs[t].as<NearPair>();
+                const NearBlockDev *nb = p->d_nblocks.as<NearBlockDev>();
+                if (!gal && t > 3) continue;
+                bool rest;
+                NearSeries S = near_series(p, t, rest);
+                if (!gal && t == TIER_SELF && kernels[w] == 1) {   // zeros
+                    S.K = 0;
+                    rest = true;
+                }
+                if (S.K > 0) {
+                    if (gal) launch_near_series_galerkin(t, p->g, p->q, p->f, S, pairs, p->npairs[t], nb, n64, n32, st);
+                    else launch_near_series(kernels[w], t, p->g, p->q, p->f, S, pairs, p->npairs[t], nb, n64, n32, st);
+                }
+                if (rest) {
+                    if (gal) launch_near_galerkin(t, p->g, p->q, p->f, S, pairs, p->npairs[t], nb, n64, n32, st);
+                    else launch_near(kernels[w], t, p->g, p->q, p->f, S, pairs, p->npairs[t], nb, n64, n32, st);
+                }
             }
             GACA_HIP_CHECK(hipGetLastError());
             GACA_HIP_CHECK(hipEventRecord(ev[2 + 2 * w], st));

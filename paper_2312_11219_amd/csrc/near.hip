@@ -6,6 +6,7 @@
 #include "galerkin_dev.h"
 #include "galerkin_p1_dev.h"
 #include "kernels.h"
+#include "near_series_dev.h"
 
 namespace gaca {
 
@@ -13,7 +14,7 @@ namespace gaca {
 // per launch.
 template <int TIER, int NF>
 __global__ void __launch_bounds__(256)
-    near_gal_kernel(GeoDev g, QuadDev q, FreqDev f, const NearPair *__restrict__ pairs,
+    near_gal_kernel(GeoDev g, QuadDev q, FreqDev f, NearSeries S, const NearPair *__restrict__ pairs,
                     int64_t npairs, const NearBlockDev *__restrict__ blocks, double2 *out64,
                     float2 *out32) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -23,7 +24,8 @@ __global__ void __launch_bounds__(256)
     NearPair pr = pairs[p];
     NearBlockDev B = blocks[pr.blk];
     const int64_t i = B.r0 + pr.i, j = B.c0 + pr.j;
-    double ar[NF], ai[NF];
+    double ar[NF], ai[NF], rc;
+    if (S.K > 0 && gal_span<TIER>(g, S, i, j, rc) <= kNearSeriesMax) return;   // near_moments.hip
     gal_near_entry<NF>(g, q, f, i, j, TIER, l0, nl, ar, ai);
     const int64_t base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
 #pragma unroll
@@ -45,24 +47,24 @@ __global__ void __launch_bounds__(256)
 }
 
 template <int T, int NF>
-static void near_gal_launch(const GeoDev &g, const QuadDev &q, const FreqDev &f,
+static void near_gal_launch(const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
                             const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks,
                             double2 *o64, float2 *o32, hipStream_t st) {
     dim3 grid((unsigned)((npairs + 255) / 256), (unsigned)((f.L_eval + NF - 1) / NF));
-    near_gal_kernel<T, NF><<<grid, 256, 0, st>>>(g, q, f, pairs, npairs, blocks, o64, o32);
+    near_gal_kernel<T, NF><<<grid, 256, 0, st>>>(g, q, f, S, pairs, npairs, blocks, o64, o32);
 }
 
-void launch_near_galerkin(int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f,
+void launch_near_galerkin(int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
                           const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks,
                           double2 *out64, float2 *out32, hipStream_t st) {
     if (npairs <= 0) return;
     switch (tier) {
-        case GT_FAR36: near_gal_launch<GT_FAR36, 8>(g, q, f, pairs, npairs, blocks, out64, out32, st); break;
-        case GT_MID: near_gal_launch<GT_MID, 4>(g, q, f, pairs, npairs, blocks, out64, out32, st); break;
-        case GT_NEAR: near_gal_launch<GT_NEAR, 2>(g, q, f, pairs, npairs, blocks, out64, out32, st); break;
-        case GT_EDGE: near_gal_launch<GT_EDGE, 2>(g, q, f, pairs, npairs, blocks, out64, out32, st); break;
-        case GT_VERTEX: near_gal_launch<GT_VERTEX, 2>(g, q, f, pairs, npairs, blocks, out64, out32, st); break;
-        default: near_gal_launch<GT_COINC, 4>(g, q, f, pairs, npairs, blocks, out64, out32, st); break;
+        case GT_FAR36: near_gal_launch<GT_FAR36, 8>(g, q, f, S, pairs, npairs, blocks, out64, out32, st); break;
+        case GT_MID: near_gal_launch<GT_MID, 4>(g, q, f, S, pairs, npairs, blocks, out64, out32, st); break;
+        case GT_NEAR: near_gal_launch<GT_NEAR, 2>(g, q, f, S, pairs, npairs, blocks, out64, out32, st); break;
+        case GT_EDGE: near_gal_launch<GT_EDGE, 2>(g, q, f, S, pairs, npairs, blocks, out64, out32, st); break;
+        case GT_VERTEX: near_gal_launch<GT_VERTEX, 2>(g, q, f, S, pairs, npairs, blocks, out64, out32, st); break;
+        default: near_gal_launch<GT_COINC, 4>(g, q, f, S, pairs, npairs, blocks, out64, out32, st); break;
     }
 }
 
@@ -81,7 +83,7 @@ __global__ void eval_gal_kernel(GeoDev g, QuadDev q, FreqDev f, int64_t n, const
 // frequencies only the first ceil(L/2) are evaluated; their conjugates fill the rest.
 template <int KERNEL, int TIER, int NF>
 __global__ void __launch_bounds__(256)
-    near_kernel(GeoDev g, QuadDev q, FreqDev f, const NearPair *__restrict__ pairs,
+    near_kernel(GeoDev g, QuadDev q, FreqDev f, NearSeries S, const NearPair *__restrict__ pairs,
                 int64_t npairs, const NearBlockDev *__restrict__ blocks, double2 *out64,
                 float2 *out32) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -91,7 +93,8 @@ __global__ void __launch_bounds__(256)
     NearPair pr = pairs[p];
     NearBlockDev B = blocks[pr.blk];
     const int64_t i = B.r0 + pr.i, j = B.c0 + pr.j;
-    double ar[NF], ai[NF];
+    double ar[NF], ai[NF], rc;
+    if (S.K > 0 && near_span(g, S, i, j, rc) <= kNearSeriesMax) return;   // near_moments.hip
     near_entry<KERNEL, NF>(g, q, f, i, j, TIER, l0, nl, ar, ai);
     const int64_t base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
 #pragma unroll
@@ -113,20 +116,20 @@ __global__ void __launch_bounds__(256)
 }
 
 template <int K, int T, int NF>
-static void near_launch(const GeoDev &g, const QuadDev &q, const FreqDev &f,
+static void near_launch(const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
                         const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks,
                         double2 *o64, float2 *o32, hipStream_t st) {
     dim3 grid((unsigned)((npairs + 255) / 256), (unsigned)((f.L_eval + NF - 1) / NF));
-    near_kernel<K, T, NF><<<grid, 256, 0, st>>>(g, q, f, pairs, npairs, blocks, o64, o32);
+    near_kernel<K, T, NF><<<grid, 256, 0, st>>>(g, q, f, S, pairs, npairs, blocks, o64, o32);
 }
 
-void launch_near(int kernel, int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f,
+void launch_near(int kernel, int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
                  const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks,
                  double2 *out64, float2 *out32, hipStream_t st) {
     if (npairs <= 0) return;
     // the expensive tiers (hundreds of points per pair) take one frequency per thread so
     // that there are enough threads; cheap tiers amortise the distance over 8 frequencies
-#define GACA_NEAR(K, T, NF) near_launch<K, T, NF>(g, q, f, pairs, npairs, blocks, out64, out32, st)
+#define GACA_NEAR(K, T, NF) near_launch<K, T, NF>(g, q, f, S, pairs, npairs, blocks, out64, out32, st)
     if (kernel == 0) {
         switch (tier) {
             case TIER_FAR6: GACA_NEAR(0, TIER_FAR6, 8); break;
@@ -149,7 +152,7 @@ void launch_near(int kernel, int tier, const GeoDev &g, const QuadDev &q, const 
 // is chosen per triangle of the column vertex's patch.
 template <int NF>
 __global__ void __launch_bounds__(256)
-    near_p1_kernel(GeoDev g, QuadDev q, FreqDev f, const NearPair *__restrict__ pairs,
+    near_p1_kernel(GeoDev g, QuadDev q, FreqDev f, NearSeries S, const NearPair *__restrict__ pairs,
                    int64_t npairs, const NearBlockDev *__restrict__ blocks, double2 *out64) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= npairs) return;
@@ -158,7 +161,8 @@ __global__ void __launch_bounds__(256)
     NearPair pr = pairs[p];
     NearBlockDev B = blocks[pr.blk];
     const int64_t i = B.r0 + pr.i, j = B.c0 + pr.j;
-    double ar[NF], ai[NF];
+    double ar[NF], ai[NF], rc;
+    if (S.K > 0 && p1_span(g, S, i, j, rc) <= kNearSeriesMax) return;   // near_moments.hip
     p1_entry<NF>(g, q, f, i, j, false, l0, nl, ar, ai);
     const int64_t base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
 #pragma unroll
@@ -172,12 +176,12 @@ __global__ void __launch_bounds__(256)
     }
 }
 
-void launch_near_p1(const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearPair *pairs,
+void launch_near_p1(const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S, const NearPair *pairs,
                     int64_t npairs, const NearBlockDev *blocks, double2 *out64, hipStream_t st) {
     if (npairs <= 0) return;
     constexpr int NF = 4;
     dim3 grid((unsigned)((npairs + 255) / 256), (unsigned)((f.L_eval + NF - 1) / NF));
-    near_p1_kernel<NF><<<grid, 256, 0, st>>>(g, q, f, pairs, npairs, blocks, out64);
+    near_p1_kernel<NF><<<grid, 256, 0, st>>>(g, q, f, S, pairs, npairs, blocks, out64);
 }
 
 __global__ void eval_p1_kernel(GeoDev g, QuadDev q, FreqDev f, int64_t n, const int32_t *rows,
