@@ -476,6 +476,7 @@ __global__ void __launch_bounds__(NT)
     const int64_t t_start = wall_clock64();
     const FarActive A = act[blockIdx.x];
     const int b = A.b;
+    if (P.declined_only && bd.st[b].rho != kFarDeclined) return;
     const FarBlockDev B = bd.blk[b];
     const int m = B.m, n = B.n;
     const int tid = threadIdx.x;

@@ -40,20 +40,36 @@ namespace gaca {
 
 namespace {
 
-// w = a / piv, rd = 1 / |piv|^2 (FP64: one reciprocal per step, by two Newton steps from the
-// hardware estimate, instead of two divisions per entry; FP32: as cdiv)
-__device__ __forceinline__ double2 row_div(double2 a, double2 p, double rd) {
-    return make_double2((a.x * p.x + a.y * p.y) * rd, (a.y * p.x - a.x * p.y) * rd);
-}
-__device__ __forceinline__ float2 row_div(float2 a, float2 p, double) { return cdiv(a, p); }
-__device__ __forceinline__ double rcp_abs2(double2 p) {
+// |piv|^2 and its reciprocal (FP64: one per step, by two Newton steps from the hardware estimate,
+// instead of two divisions per entry; FP32: unused, as cdiv)
+struct Den {
+    double d, rd;
+};
+__device__ __forceinline__ Den den(double2 p) {
     const double d = cabs2(p);
-    if (!(d > 1e-290 && d < 1e290)) return 1.0 / d;   // the estimate's range, NaN
+    if (!(d > 1e-290 && d < 1e290)) return {d, 0.0};   // beyond the estimate's range, NaN: divisions
     double t = __builtin_amdgcn_rcp(d);
     t = fma(t, fma(-d, t, 1.0), t);
-    return fma(t, fma(-d, t, 1.0), t);
+    return {d, fma(t, fma(-d, t, 1.0), t)};
 }
-__device__ __forceinline__ double rcp_abs2(float2) { return 0.0; }
+__device__ __forceinline__ Den den(float2) { return {0.0, 0.0}; }
+
+// w = a / piv.  EXACT: the quotients corrected by their remainder (Markstein), which rounds them as
+// a division does.  Small faces of flat pieces have entries that vanish up to rounding; whether a
+// residual row is then exactly zero (and skipped) or not hangs on that rounding.
+template <bool EXACT>
+__device__ __forceinline__ double2 row_div(double2 a, double2 p, Den q) {
+    const double nr = a.x * p.x + a.y * p.y, ni = a.y * p.x - a.x * p.y;
+    if (q.rd == 0.0) return make_double2(nr / q.d, ni / q.d);
+    double wr = nr * q.rd, wi = ni * q.rd;
+    if (EXACT) {
+        wr = fma(fma(-q.d, wr, nr), q.rd, wr);
+        wi = fma(fma(-q.d, wi, ni), q.rd, wi);
+    }
+    return make_double2(wr, wi);
+}
+template <bool EXACT>
+__device__ __forceinline__ float2 row_div(float2 a, float2 p, Den) { return cdiv(a, p); }
 
 // r - u w.  Small faces come close to full rank, where the residual is rounding: there the
 // product is rounded before it is subtracted, as u w is where the expansion sums it (WHOLE);
@@ -183,6 +199,32 @@ __global__ void __launch_bounds__(NT, MINW)
             const int i = tr + TR * x, j = tc + TC * y;
             rr[x][y] = i < m && j < n ? R[i * n + j] : czero<FT>();
         }
+    // Operators with normals vanish, up to rounding, between coplanar elements.  In a face with such
+    // entries a row ends as rounding or as exact zero by the order of its sums, which decides where
+    // the ACA stops: the larger ones are left to the kernel that forms a row from its history, as
+    // the expansion sums it (far_aca_large_kernel; the smaller ones keep that order here).
+    if (!EMIT && !MIXED && P.decline) {
+        double top = 0.0, low = INFINITY;
+        const int mo = opaque(m), no = opaque(n);
+#pragma unroll
+        for (int x = 0; x < RX; ++x) {
+#pragma unroll
+            for (int y = 0; y < CY; ++y)
+                if (tr + TR * x < mo && tc + TC * y < no) {
+                    const double a = cabs2(rr[x][y]);
+                    top = fmax(top, a);
+                    low = fmin(low, a);
+                }
+            fence();
+        }
+        double nlow = -low, dummy = 0.0;
+        red.maxsum(top, dummy);
+        red.maxsum(nlow, dummy);
+        if (-nlow < 1e-26 * top) {
+            if (tid == 0) bd.st[b].rho = kFarDeclined;
+            return;
+        }
+    }
     for (int t = tid; t < 64 * KN; t += NT) rowb[0][t] = rowb[1][t] = czero<FT>();
     for (int t = tid; t < 64 * KM; t += NT) ucol[t] = czero<FT>();
     unsigned long long colm[KN], freem[KM];   // columns of the face; rows not used yet
@@ -270,14 +312,14 @@ __global__ void __launch_bounds__(NT, MINW)
                     for (int x = 0; x < RX; ++x) ucol[tr + TR * x] = rr[x][y];
         }
         const FT piv = rowv[jp];
-        const double rd = rcp_abs2(piv);
+        const Den rd = den(piv);
         if (wave == 0)
 #pragma unroll
             for (int k = 0; k < KN; ++k)
-                if (lane + 64 * k < n) Wb[(int64_t)q * n + lane + 64 * k] = row_div(rowv[lane + 64 * k], piv, rd);
+                if (lane + 64 * k < n) Wb[(int64_t)q * n + lane + 64 * k] = row_div<EMIT>(rowv[lane + 64 * k], piv, rd);
         FT wy[CY];
 #pragma unroll
-        for (int y = 0; y < CY; ++y) wy[y] = row_div(rowv[tc + TC * y], piv, rd);
+        for (int y = 0; y < CY; ++y) wy[y] = row_div<EMIT>(rowv[tc + TC * y], piv, rd);
         __syncthreads();
         double u2[KM];
         unsigned hu = 0, ha = 0;   // maxima over the unused rows, over all rows
@@ -309,7 +351,7 @@ __global__ void __launch_bounds__(NT, MINW)
             for (int k = 0; k < KM; ++k) nu2 += u2[k];
 #pragma unroll
             for (int k = 0; k < KN; ++k)
-                if (lane + 64 * k < n) nw2 += cabs2(row_div(rowv[lane + 64 * k], piv, rd));
+                if (lane + 64 * k < n) nw2 += cabs2(row_div<EMIT>(rowv[lane + 64 * k], piv, rd));
             const double t2 = wave_sum(nu2) * wave_sum(nw2), tt = sqrt(t2);
             s_lo = fmax(0.0, s_lo - tt);
             if (!(t2 > eps2 * (ref2 + s_hi * s_hi) * (1.0 + 1e-9))) {
@@ -344,6 +386,32 @@ __global__ void __launch_bounds__(NT, MINW)
     int pidx = 0;
     double mxh = 0.0, h2 = 0.0;
     if (EMIT && q > 0) {
+        // H_l = sum_q u_q w_q in the order of the steps (the face less its residual would carry the
+        // face's rounding)
+#pragma unroll
+        for (int x = 0; x < RX; ++x)
+#pragma unroll
+            for (int y = 0; y < CY; ++y) rr[x][y] = czero<FT>();
+        __syncthreads();   // U and W of every wave
+        constexpr int PU = RX * CY <= 16 ? 2 : 1;   // steps whose loads are in flight
+        for (int p0 = 0; p0 < q; p0 += PU) {
+            FT up[PU][RX], wp[PU][CY];
+#pragma unroll
+            for (int t = 0; t < PU; ++t) {
+                const int p = min(p0 + t, q - 1);
+#pragma unroll
+                for (int x = 0; x < RX; ++x) up[t][x] = Ub[(int64_t)p * m + min(tr + TR * x, m - 1)];
+#pragma unroll
+                for (int y = 0; y < CY; ++y) wp[t][y] = Wb[(int64_t)p * n + min(tc + TC * y, n - 1)];
+            }
+#pragma unroll
+            for (int t = 0; t < PU; ++t)
+                if (p0 + t < q)
+#pragma unroll
+                    for (int x = 0; x < RX; ++x)
+#pragma unroll
+                        for (int y = 0; y < CY; ++y) rr[x][y] = cadd(rr[x][y], cmul(up[t][x], wp[t][y]));
+        }
         const int mo = opaque(m), no = opaque(n);
 #pragma unroll
         for (int x = 0; x < RX; ++x) {
@@ -351,10 +419,8 @@ __global__ void __launch_bounds__(NT, MINW)
             for (int y = 0; y < CY; ++y) {
                 const int ie = tr + TR * x, j = tc + TC * y;
                 if (ie < mo && j < no) {
-                    const FT s = csub(R[ie * no + j], rr[x][y]);
-                    R[ie * no + j] = s;
-                    rr[x][y] = s;
-                    const double s2 = cabs2(s);
+                    R[ie * no + j] = rr[x][y];
+                    const double s2 = cabs2(rr[x][y]);
                     mxh = fmax(mxh, s2);
                     h2 += s2;
                 }

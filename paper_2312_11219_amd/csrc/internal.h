@@ -138,6 +138,9 @@ struct AcaParams {
     int32_t zero_batch;        // several rows per pass in the large-face zero-row search
     int32_t recompress;        // faces recompressed after their ACA
     int32_t pivot_index;       // pivot by the eq. (index) row estimate
+    int32_t decline;           // register kernels: 1 mark faces with vanishing entries kFarDeclined
+    int32_t declined_only;     // kernels in HBM: 1 take the marked faces alone
 };
+constexpr int32_t kFarDeclined = -1;   // FarStateDev::rho of a face that its kernel has left
 
 }  // namespace gaca

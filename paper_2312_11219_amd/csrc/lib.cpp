@@ -1399,6 +1399,8 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
     for (gaca_hmatrix *hh : H) hh->eps_aca_used = P.eps_aca;
     P.rcap = rcap;
     P.kernel = fk;
+    // entries vanish for the operators with normals and in given tensors, not for the single layers
+    P.decline = !mixed && (dense || !(fk == 0 || fk == 2)) ? 1 : 0;
     P.zero_batch = p->opt.zero_rows_batch != 0;
     P.recompress = p->opt.recompress != 0;
     P.pivot_index = p->opt.pivot_estimate != 0;
@@ -1815,6 +1817,12 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
                 ccls[k] += gcnt[g];
                 if (g < 4) continue;
                 launch_far_aca_reg(reg_cls(g), P, bd, dact + gfirst[g], gcnt[g], ks[k]);
+                if (P.decline && kFarRegSide[reg_cls(g)] > kFarEmitSide) {
+                    AcaParams Q = P;
+                    Q.declined_only = 1;
+                    launch_far_aca(1, 256, Q, bd, dact + gfirst[g], gcnt[g], ks[k]);
+                    ++nl;
+                }
             }
             // Gram rows of the faces that are not expanded, after the ACAs of their class
             if (!recomp)
