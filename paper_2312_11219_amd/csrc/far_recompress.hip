@@ -14,8 +14,8 @@
 // pairs, until a sweep rotates no pair with |k_p^H k_q| > 1e-15 ||k_p|| ||k_q||.  All in
 // FP64 (the mixed path's FP32 factors are widened and the results rounded back).
 // Faces of rank 1 are already in that form; faces of rank above kRecMaxRank are kept as
-// computed.  Faces with sides up to 32 take the LDS kernel below; for the others one workgroup per
-// face, grid-stride over the active faces, each workgroup with
+// computed.  Faces with sides up to 32 or ranks up to 48 take the LDS kernel below; the others one
+// workgroup per face, grid-stride over the active faces, each workgroup with
 // its own slot of 6 kRecMaxRank^2 complex doubles of workspace (R_U, R_W, K, V, A_U, B_W);
 // the old factors are copied to the face's H slot (m n >= rho max(m, n)) while the new
 // ones are written in place.
@@ -114,7 +114,7 @@ __device__ void cholesky_upper(double2 *G, int rho, double *dsc) {
 template <bool MIXED>
 __global__ void __launch_bounds__(256) far_recompress_kernel(AcaParams P, FarBatchDev bd,
                                                              const FarActive *act, int nact,
-                                                             double2 *ws) {
+                                                             double2 *ws, int rlo) {
     using FT = rface_t<MIXED>;
     constexpr int RM = kRecMaxRank;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(256) far_recompress_kernel(AcaParams P, FarBat
         const FarActive A = act[a];
         const int b = A.b;
         const int rho = bd.st[b].rho;
-        if (rho < 2 || rho > RM) continue;
+        if (rho < rlo || rho > RM) continue;
         const FarBlockDev B = bd.blk[b];
         const int m = B.m, n = B.n;
         FT *U = reinterpret_cast<FT *>(bd.uw) + B.uw_off;
@@ -288,17 +288,23 @@ __device__ __forceinline__ double rsq2(double x) {
 // (dot products, rotation, update).  1614 faces of up to 24 x 24, rank 21 before the truncation
 // (768-triangle cube): 336 us a launch, in the general kernel 2570 us; one wave per face
 // took 402 us, a launch each for ranks up to 16 and above 500 us (few faces are below).
-template <bool MIXED, int RM>
-__global__ void __launch_bounds__(128) far_recompress_small_kernel(AcaParams P, FarBatchDev bd,
-                                                                   const FarActive *act) {
+//
+// Larger faces (BIG) of rank rlo to RM: the factors pass through the same space RM columns at a
+// time, their rows are taken in turn at the end; with RM = 48 four waves (24 pairs of columns) have a
+// CU to themselves.  Two faces of 48 rows beside 310 of 24 (768-triangle cube): 2910 us a launch in
+// the general kernel, 680 us here; the build 33.3 -> 13.3 ms with the small faces beside them.
+template <bool MIXED, int RM, int NT, bool BIG>
+__global__ void __launch_bounds__(NT) far_recompress_small_kernel(AcaParams P, FarBatchDev bd, const FarActive *act,
+                                                                  int rlo) {
     using FT = rface_t<MIXED>;
     constexpr int LD = RM + 1;   // column stride: no power of two banks apart
     constexpr int LP = 8;                 // lanes per pair (at most 16 pairs)
-    static_assert(RM <= 32, "sixteen pairs of columns a round");
-    const int tid = threadIdx.x, half = tid >> 6, hl = tid & 63;
+    constexpr int HN = NT / 2;            // threads per factor
+    static_assert(RM / 2 * LP <= NT && RM <= 64, "all pairs of a round at once, a lane per column");
+    const int tid = threadIdx.x, half = (tid >> 6) & 1, hl = (tid & 63) + 64 * (tid >> 7);
     const int b = act[blockIdx.x].b;
     const int rho = bd.st[b].rho;
-    if (rho < 2) return;
+    if (rho < rlo || (BIG && rho > RM)) return;
     const FarBlockDev B = bd.blk[b];
     const int m = B.m, n = B.n;
     FT *U = reinterpret_cast<FT *>(bd.uw) + B.uw_off;
@@ -309,24 +315,26 @@ __global__ void __launch_bounds__(128) far_recompress_small_kernel(AcaParams P, 
     // the factors staged in K and V (rows of stride LD), a wave for each
     double2 *F = half ? V : K, *G = R2[half];
     const int len = half ? n : m;
-    {
+    for (int i0 = 0; i0 < (BIG ? max(m, n) : 1); i0 += RM) {
+        const int ln = BIG ? max(0, min(RM, len - i0)) : len;
         const FT *src = half ? W : U;
-        for (int e = hl; e < rho * len; e += 64) {
-            const int p = e / len;
-            F[p * LD + e - p * len] = to_d2(src[e]);
+        if (BIG && i0 > 0) __syncthreads();   // the last columns are summed
+        for (int e = hl; e < rho * ln; e += HN) {
+            const int p = e / ln;
+            F[p * LD + e - p * ln] = to_d2(src[(int64_t)p * len + i0 + e - p * ln]);
         }
-    }
-    __syncthreads();
-    // Gram matrix G[q LD + p] = sum_i conj(F[p][i]) F[q][i], p <= q
-    for (int e = hl; e < rho * (rho + 1) / 2; e += 64) {
-        int q = (int)((sqrtf(8.0f * e + 1.0f) - 1.0f) * 0.5f);
-        while ((q + 1) * (q + 2) / 2 <= e) ++q;
-        while (q * (q + 1) / 2 > e) --q;
-        const int p = e - q * (q + 1) / 2;
-        double2 s = make_double2(0.0, 0.0);
+        __syncthreads();
+        // Gram matrix G[q LD + p] = sum_i conj(F[p][i]) F[q][i], p <= q
+        for (int e = hl; e < rho * (rho + 1) / 2; e += HN) {
+            int q = (int)((sqrtf(8.0f * e + 1.0f) - 1.0f) * 0.5f);
+            while ((q + 1) * (q + 2) / 2 <= e) ++q;
+            while (q * (q + 1) / 2 > e) --q;
+            const int p = e - q * (q + 1) / 2;
+            double2 s = BIG && i0 > 0 ? G[q * LD + p] : make_double2(0.0, 0.0);
 #pragma unroll 4
-        for (int i = 0; i < len; ++i) s = cadd(s, cconjmul(F[p * LD + i], F[q * LD + i]));
-        G[q * LD + p] = s;
+            for (int i = 0; i < ln; ++i) s = cadd(s, cconjmul(F[p * LD + i], F[q * LD + i]));
+            G[q * LD + p] = s;
+        }
     }
     __syncthreads();
     // Cholesky factor of the column-scaled matrix, a lane per column
@@ -361,7 +369,7 @@ __global__ void __launch_bounds__(128) far_recompress_small_kernel(AcaParams P, 
     __syncthreads();
     const double2 *RU = R2[0], *RW = R2[1];
     // K = R_U R_W^T, V = I (columns of stride LD)
-    for (int e = tid; e < rho * rho; e += 128) {
+    for (int e = tid; e < rho * rho; e += NT) {
         const int q = e / rho, p = e - q * rho;
         double2 s = make_double2(0.0, 0.0);
         for (int k = max(p, q); k < rho; ++k) s = cadd(s, cmul_d(RU[k * LD + p], RW[k * LD + q]));
@@ -456,11 +464,11 @@ __global__ void __launch_bounds__(128) far_recompress_small_kernel(AcaParams P, 
         --rk;
     }
     // A_U = R_W^T V_r over V and B_W = R_U^T conj((K V)_r) Sigma_r^{-2} over K (rho x rk)
-    constexpr int PER = (RM * RM + 127) / 128;
+    constexpr int PER = (RM * RM + NT - 1) / NT;
     double2 au[PER], bw[PER];
 #pragma unroll
     for (int t = 0; t < PER; ++t) {
-        const int e = tid + 128 * t;
+        const int e = tid + NT * t;
         au[t] = bw[t] = make_double2(0.0, 0.0);
         if (e < rho * rk) {
             const int c = e / rho, k = e - c * rho, oc = order[c];
@@ -476,7 +484,7 @@ __global__ void __launch_bounds__(128) far_recompress_small_kernel(AcaParams P, 
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < PER; ++t) {
-        const int e = tid + 128 * t;
+        const int e = tid + NT * t;
         if (e < rho * rk) {
             const int c = e / rho, k = e - c * rho;
             V[c * LD + k] = au[t];
@@ -484,37 +492,47 @@ __global__ void __launch_bounds__(128) far_recompress_small_kernel(AcaParams P, 
         }
     }
     __syncthreads();
-    // U' = U A_U and W' = W B_W: a lane holds row hl of the old factor while it writes the new
+    // U' = U A_U and W' = W B_W: a lane holds a row of the old factor while it writes the new
     FT *out = half ? W : U;
     const double2 *Tm = half ? K : V;
-    if (hl < len) {
+    for (int row = hl; row < len; row += HN) {
         double2 f[RM];
 #pragma unroll
-        for (int k = 0; k < RM; ++k) f[k] = k < rho ? to_d2(out[k * len + hl]) : make_double2(0.0, 0.0);
+        for (int k = 0; k < RM; ++k) f[k] = k < rho ? to_d2(out[(int64_t)k * len + row]) : make_double2(0.0, 0.0);
         for (int c = 0; c < rk; ++c) {
             double2 acc = make_double2(0.0, 0.0);
 #pragma unroll
             for (int k = 0; k < RM; ++k)
                 if (k < rho) acc = cadd(acc, cmul_d(f[k], Tm[c * LD + k]));
-            out[c * len + hl] = from_d2<FT>(acc);
+            out[(int64_t)c * len + row] = from_d2<FT>(acc);
         }
     }
     if (tid == 0) bd.st[b].rho = rk;
 }
 
-void launch_far_recompress(const AcaParams &P, const FarBatchDev &bd, const FarActive *act,
-                           int nact, double2 *ws, int nslot, hipStream_t st) {
-    if (nact <= 0) return;
-    const int g = nact < nslot ? nact : nslot;
-    if (bd.mixed) far_recompress_kernel<true><<<g, 256, 0, st>>>(P, bd, act, nact, ws);
-    else far_recompress_kernel<false><<<g, 256, 0, st>>>(P, bd, act, nact, ws);
-}
-
 template <bool MX>
 static void small_dispatch(int side, const AcaParams &P, const FarBatchDev &bd, const FarActive *act, int nact,
                            hipStream_t st) {
-    if (side <= 24) far_recompress_small_kernel<MX, 24><<<nact, 128, 0, st>>>(P, bd, act);
-    else far_recompress_small_kernel<MX, 32><<<nact, 128, 0, st>>>(P, bd, act);
+    if (side <= 24) far_recompress_small_kernel<MX, 24, 128, false><<<nact, 128, 0, st>>>(P, bd, act, 2);
+    else far_recompress_small_kernel<MX, 32, 128, false><<<nact, 128, 0, st>>>(P, bd, act, 2);
+}
+
+// Faces with sides above 32 by their rank (each launch leaves the faces of the others): up to 32 and
+// up to 48 in LDS, above in the workspace
+template <bool MX>
+static void big_dispatch(const AcaParams &P, const FarBatchDev &bd, const FarActive *act, int nact, double2 *ws,
+                         int nslot, hipStream_t st) {
+    far_recompress_small_kernel<MX, 32, 128, true><<<nact, 128, 0, st>>>(P, bd, act, 2);
+    far_recompress_small_kernel<MX, 48, 256, true><<<nact, 256, 0, st>>>(P, bd, act, 33);
+    const int g = nact < nslot ? nact : nslot;
+    far_recompress_kernel<MX><<<g, 256, 0, st>>>(P, bd, act, nact, ws, 49);
+}
+
+void launch_far_recompress(const AcaParams &P, const FarBatchDev &bd, const FarActive *act,
+                           int nact, double2 *ws, int nslot, hipStream_t st) {
+    if (nact <= 0) return;
+    if (bd.mixed) big_dispatch<true>(P, bd, act, nact, ws, nslot, st);
+    else big_dispatch<false>(P, bd, act, nact, ws, nslot, st);
 }
 
 void launch_far_recompress_small(int side, const AcaParams &P, const FarBatchDev &bd,

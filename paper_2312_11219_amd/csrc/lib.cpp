@@ -1474,7 +1474,7 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
     // HBM, on the main far stream)
     const hipStream_t ks[4] = {p->far_streams[3], p->far_streams[2], p->far_streams[1], s0};
     enum { EV_BEGIN, EV_END, EV_F0, EV_F1, EV_K0, EV_K1, EV_K2, EV_K3, EV_S0, EV_S1, EV_S2, EV_S3, EV_J, EV_X,
-           EV_T, EV_C, EV_P0, EV_P2, EV_N };
+           EV_T, EV_C, EV_P0, EV_P2, EV_R, EV_N };
     hipEvent_t ev[EV_N];
     for (auto &e : ev) GACA_HIP_CHECK(hipEventCreate(&e));
     struct EvGuard {
@@ -1849,13 +1849,21 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
                 copy_ev = true;
             }
             if (recomp) {
-                // the classes of sides up to 32 (the last groups) one wave per face, in LDS
+                // the classes of sides up to 32 (the last groups), beside the larger faces if there
+                // are any: few of those, they leave most CUs idle
                 constexpr int g32 = 4 + kFarRegClasses - 2, g24 = g32 + 1;
                 static_assert(kFarRegSide[1] == 32 && kFarRegSide[0] == 24, "sides of the last two groups");
                 launch_far_recompress(P, bd, dact, gfirst[g32], W.rec_ws.as<double2>(), kRecSlots, s0);
-                launch_far_recompress_small(32, P, bd, dact + gfirst[g32], gcnt[g32], s0);
-                launch_far_recompress_small(24, P, bd, dact + gfirst[g24], gcnt[g24], s0);
-                n_launch += (gfirst[g32] > 0) + (gcnt[g32] > 0) + (gcnt[g24] > 0);
+                const bool beside = gfirst[g32] > 0 && gfirst[kGroups] > gfirst[g32];
+                const hipStream_t rs = beside ? ks[2] : s0;
+                if (beside) GACA_HIP_CHECK(hipStreamWaitEvent(rs, ev[EV_K0], 0));
+                launch_far_recompress_small(32, P, bd, dact + gfirst[g32], gcnt[g32], rs);
+                launch_far_recompress_small(24, P, bd, dact + gfirst[g24], gcnt[g24], rs);
+                if (beside) {
+                    GACA_HIP_CHECK(hipEventRecord(ev[EV_R], rs));
+                    GACA_HIP_CHECK(hipStreamWaitEvent(s0, ev[EV_R], 0));
+                }
+                n_launch += 3 * (gfirst[g32] > 0) + (gcnt[g32] > 0) + (gcnt[g24] > 0);
             }
             launch_far_expand(bd, dact, ntile, s0);
             GACA_HIP_CHECK(hipEventRecord(ev[EV_X], s0));
