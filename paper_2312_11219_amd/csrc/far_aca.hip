@@ -15,7 +15,7 @@
 //
 // The face phase evaluates every entry of every active face in parallel (the kernel
 // evaluations are most of the arithmetic); only the ACA of one face is sequential and runs
-// one workgroup per block.  Faces with sides up to 160 (mixed 192) are held in registers
+// one workgroup per block.  Faces with sides up to 128 (mixed 192) are held in registers
 // through it (far_aca_reg.hip), larger ones keep R in HBM; above sides of 64 H_l is formed by
 // the tiled expand phase.
 //

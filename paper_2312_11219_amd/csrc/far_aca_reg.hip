@@ -1,4 +1,4 @@
-// Face ACA with the residual face in registers (faces with both sides up to 160 in FP64, 192 in
+// Face ACA with the residual face in registers (faces with both sides up to 128 in FP64, 192 in
 // the mixed path): the partial-pivot ACA of one face by one workgroup, in place.
 //
 // The face is spread over the workgroup as a TR x TC grid of threads, thread (tr, tc) owning
@@ -27,8 +27,9 @@
 //
 // Device clocks per face in whole FP64 builds (all classes running), with R and S in registers or R
 // in HBM before: 24 x 24 (rank 21, 3072-triangle cube) 64 -> 37 us, 48 x 48 (31) 114 -> 83 us,
-// 96 x 96 (46) 400 -> 100 us; 147 x 147 (36, 9408-triangle sphere) 190 us.  Builds: cube, both
-// operators, 51 -> 41 ms; sphere 149 -> 125 ms.
+// 96 x 96 (46) 400 -> 100 us.  FP64 faces of 160 x 160 took 190 us for 400, but with 67 registers
+// spilled the face rank changed from build to build in one of a million faces (delta_zero 1e-7, where
+// rows of zeros are skipped); no class here spills.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -393,24 +394,18 @@ __global__ void __launch_bounds__(NT, MINW)
 #pragma unroll
             for (int y = 0; y < CY; ++y) rr[x][y] = czero<FT>();
         __syncthreads();   // U and W of every wave
-        constexpr int PU = RX * CY <= 16 ? 2 : 1;   // steps whose loads are in flight
-        for (int p0 = 0; p0 < q; p0 += PU) {
-            FT up[PU][RX], wp[PU][CY];
+        for (int p = 0; p < q; ++p) {
+            const FT *up = Ub + (int64_t)p * m, *wp = Wb + (int64_t)p * n;
+            FT w[CY];
 #pragma unroll
-            for (int t = 0; t < PU; ++t) {
-                const int p = min(p0 + t, q - 1);
+            for (int y = 0; y < CY; ++y) w[y] = wp[min(tc + TC * y, n - 1)];
 #pragma unroll
-                for (int x = 0; x < RX; ++x) up[t][x] = Ub[(int64_t)p * m + min(tr + TR * x, m - 1)];
+            for (int x = 0; x < RX; ++x) {
+                const FT u = up[min(tr + TR * x, m - 1)];
 #pragma unroll
-                for (int y = 0; y < CY; ++y) wp[t][y] = Wb[(int64_t)p * n + min(tc + TC * y, n - 1)];
+                for (int y = 0; y < CY; ++y) rr[x][y] = cadd(rr[x][y], cmul(u, w[y]));
+                if (RX * CY >= 32 && x % 2) fence();   // no more than two u in flight (registers)
             }
-#pragma unroll
-            for (int t = 0; t < PU; ++t)
-                if (p0 + t < q)
-#pragma unroll
-                    for (int x = 0; x < RX; ++x)
-#pragma unroll
-                        for (int y = 0; y < CY; ++y) rr[x][y] = cadd(rr[x][y], cmul(up[t][x], wp[t][y]));
         }
         const int mo = opaque(m), no = opaque(n);
 #pragma unroll
@@ -449,22 +444,27 @@ __global__ void __launch_bounds__(NT, MINW)
     }
 }
 
-// One class of faces: both sides at most kFarRegSide[c].  Up to 48 one wave per face (9, 16, 25,
-// 36 entries a lane); above, the threads that keep about 25 to 50 entries each: fewer would
+// One class of faces: both sides at most kFarRegSide[c].  Up to 40 (mixed 48) one wave per face (9,
+// 16, 25, 36 entries a lane); above, the threads that keep about 25 to 50 entries each: fewer would
 // spill, more would repeat the reductions on more waves.
 template <bool MX>
 void reg_dispatch(int c, const AcaParams &P, const FarBatchDev &bd, const FarActive *act, int nact,
                   hipStream_t st) {
     switch (c) {
-        case 0: far_aca_reg_kernel<64, 8, 3, 3, 4, MX, true><<<nact, 64, 0, st>>>(P, bd, act); break;
+        case 0: far_aca_reg_kernel<64, 8, 3, 3, MX ? 4 : 3, MX, true><<<nact, 64, 0, st>>>(P, bd, act); break;
         case 1: far_aca_reg_kernel<64, 8, 4, 4, 3, MX, true><<<nact, 64, 0, st>>>(P, bd, act); break;
         case 2: far_aca_reg_kernel<64, 8, 5, 5, 2, MX, true><<<nact, 64, 0, st>>>(P, bd, act); break;
-        case 3: far_aca_reg_kernel<64, 8, 6, 6, 2, MX, true><<<nact, 64, 0, st>>>(P, bd, act); break;
+        case 3:   // FP64: 36 entries a lane spill
+            if constexpr (MX) far_aca_reg_kernel<64, 8, 6, 6, 2, MX, true><<<nact, 64, 0, st>>>(P, bd, act);
+            else far_aca_reg_kernel<128, 8, 6, 3, 2, MX, true><<<nact, 128, 0, st>>>(P, bd, act);
+            break;
         case 4: far_aca_reg_kernel<128, 8, 8, 4, 2, MX, true><<<nact, 128, 0, st>>>(P, bd, act); break;
         case 5: far_aca_reg_kernel<256, 16, 5, 5, 2, MX, false><<<nact, 256, 0, st>>>(P, bd, act); break;
         case 6: far_aca_reg_kernel<256, 16, 6, 6, 2, MX, false><<<nact, 256, 0, st>>>(P, bd, act); break;
         case 7: far_aca_reg_kernel<512, 16, 8, 4, 2, MX, false><<<nact, 512, 0, st>>>(P, bd, act); break;
-        case 8: far_aca_reg_kernel<512, 16, 10, 5, 2, MX, false><<<nact, 512, 0, st>>>(P, bd, act); break;
+        case 8:
+            if constexpr (MX) far_aca_reg_kernel<512, 16, 10, 5, 2, MX, false><<<nact, 512, 0, st>>>(P, bd, act);
+            break;
         default:
             if constexpr (MX) far_aca_reg_kernel<512, 16, 12, 6, 2, MX, false><<<nact, 512, 0, st>>>(P, bd, act);
             break;

@@ -165,8 +165,8 @@ void launch_far_map(const FarBatchDev &bd, const FarActive *act, int nact, int n
 void launch_far_face(int kernel, const GeoDev &g, const FreqDev &f, const FarBatchDev &bd,
                      const FarActive *act, int64_t nchunk, hipStream_t st);
 // Faces in registers (csrc/far_aca_reg.hip): class c takes both sides <= kFarRegSide[c]; the
-// mixed path all classes, FP64 all but the last (a face of 192 x 192 double2 exceeds the
-// registers of a CU).  Classes up to kFarEmitSide store H_l themselves.
+// mixed path all classes, FP64 all but the last two (160 x 160 double2 and the rest of a thread's
+// state exceed the registers of a CU).  Classes up to kFarEmitSide store H_l themselves.
 constexpr int kFarRegClasses = 10;
 constexpr int kFarRegSide[kFarRegClasses] = {24, 32, 40, 48, 64, 80, 96, 128, 160, 192};
 constexpr int kFarEmitSide = 64;
