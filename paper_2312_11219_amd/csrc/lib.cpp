@@ -1794,33 +1794,44 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
                 // the previous faces read once, the new face written once
                 by_face += mn * (ell_h[lb] + 1.0) * fe_bytes;
             }
-            for (int k = 0; k < 3; ++k) GACA_HIP_CHECK(hipStreamWaitEvent(ks[k], ev[EV_F1], 0));
+            int nl = 0, ccls[4] = {0, 0, 0, 0}, ncls = 0;
+            for (int g = 0; g < kGroups; ++g)
+                if (gcnt[g] > 0) ccls[aca_class(g)] += gcnt[g];
+            for (int k = 0; k < 4; ++k) ncls += ccls[k] > 0;
+            // faces of one class: their launches follow the face kernel on its stream (going to
+            // another one and back cost 0.1 ms of the 0.18 of an iteration on 300 triangles)
+            const bool multi = ncls > 1;
+            hipStream_t cs[4];
+            for (int k = 0; k < 4; ++k) cs[k] = multi ? ks[k] : s0;
             // this iteration's ACAs write the U, W slot that the previous iteration's copy
-            // reads (on ks[0], in order before the class-0 launches)
-            if (copy_ev)
-                for (int k = 1; k < 4; ++k) GACA_HIP_CHECK(hipStreamWaitEvent(ks[k], ev[EV_C], 0));
-            // class k's launches run between EV_S0 + k and EV_K0 + k on ks[k] (after its waits)
-            for (int k = 0; k < 4; ++k) GACA_HIP_CHECK(hipEventRecord(ev[EV_S0 + k], ks[k]));
-            int nl = 0, ccls[4] = {0, 0, 0, 0};
+            // reads (on ks[0], in order before the class-0 launches there)
+            const bool copying = copy_ev && hipEventQuery(ev[EV_C]) != hipSuccess;
+            if (copying) (void)hipGetLastError();   // hipErrorNotReady
+            for (int k = 0; k < 4; ++k) {
+                if (ccls[k] == 0) continue;
+                if (cs[k] != s0) GACA_HIP_CHECK(hipStreamWaitEvent(cs[k], ev[EV_F1], 0));
+                if (copying && cs[k] != ks[0]) GACA_HIP_CHECK(hipStreamWaitEvent(cs[k], ev[EV_C], 0));
+                // class k's launches run between EV_S0 + k and EV_K0 + k (after its waits)
+                if (multi) GACA_HIP_CHECK(hipEventRecord(ev[EV_S0 + k], cs[k]));
+            }
             // faces in HBM by path (general, several entries, one entry per thread), one after
             // the other on ks[3]: 512 threads and ~104 KB of LDS history, one face per CU
-            launch_far_aca(0, tlx, P, bd, dact, gcnt[0], ks[3]);
-            GACA_HIP_CHECK(hipEventRecord(ev[EV_P0], ks[3]));
-            launch_far_aca(2, tlx, P, bd, dact + gfirst[1], gcnt[1], ks[3]);
-            GACA_HIP_CHECK(hipEventRecord(ev[EV_P2], ks[3]));
-            launch_far_aca(1, tlx, P, bd, dact + gfirst[2], gcnt[2], ks[3]);
-            launch_far_aca(1, 256, P, bd, dact + gfirst[3], gcnt[3], ks[2]);
+            launch_far_aca(0, tlx, P, bd, dact, gcnt[0], cs[3]);
+            if (ccls[3]) GACA_HIP_CHECK(hipEventRecord(ev[EV_P0], cs[3]));
+            launch_far_aca(2, tlx, P, bd, dact + gfirst[1], gcnt[1], cs[3]);
+            if (ccls[3]) GACA_HIP_CHECK(hipEventRecord(ev[EV_P2], cs[3]));
+            launch_far_aca(1, tlx, P, bd, dact + gfirst[2], gcnt[2], cs[3]);
+            launch_far_aca(1, 256, P, bd, dact + gfirst[3], gcnt[3], cs[2]);
             for (int g = 0; g < kGroups; ++g) {
                 if (gcnt[g] == 0) continue;
                 ++nl;
                 const int k = aca_class(g);
-                ccls[k] += gcnt[g];
                 if (g < 4) continue;
-                launch_far_aca_reg(reg_cls(g), P, bd, dact + gfirst[g], gcnt[g], ks[k]);
+                launch_far_aca_reg(reg_cls(g), P, bd, dact + gfirst[g], gcnt[g], cs[k]);
                 if (P.decline && kFarRegSide[reg_cls(g)] > kFarEmitSide) {
                     AcaParams Q = P;
                     Q.declined_only = 1;
-                    launch_far_aca(1, 256, Q, bd, dact + gfirst[g], gcnt[g], ks[k]);
+                    launch_far_aca(1, 256, Q, bd, dact + gfirst[g], gcnt[g], cs[k]);
                     ++nl;
                 }
             }
@@ -1834,12 +1845,15 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
                             g1 = g + 1;
                         }
                     const int cn = gfirst[g1] - gfirst[g0];
-                    launch_far_gram_small(bd, dact + gfirst[g0], cn, ks[k]);
+                    launch_far_gram_small(bd, dact + gfirst[g0], cn, cs[k]);
                     nl += cn > 0;
                 }
             GACA_HIP_CHECK(hipGetLastError());
-            for (int k = 0; k < 4; ++k) GACA_HIP_CHECK(hipEventRecord(ev[EV_K0 + k], ks[k]));
-            for (int k = 0; k < 3; ++k) GACA_HIP_CHECK(hipStreamWaitEvent(s0, ev[EV_K0 + k], 0));
+            for (int k = 0; k < 4 && multi; ++k) {
+                if (ccls[k] == 0) continue;
+                GACA_HIP_CHECK(hipEventRecord(ev[EV_K0 + k], cs[k]));
+                if (cs[k] != s0) GACA_HIP_CHECK(hipStreamWaitEvent(s0, ev[EV_K0 + k], 0));
+            }
             GACA_HIP_CHECK(hipEventRecord(ev[EV_J], s0));
             // the factors accepted in the previous iteration (its U, W slot) -> arena, on ks[0]
             // after the class-0 ACAs: the copy runs beside the large-face ACAs (latency bound)
@@ -1890,14 +1904,14 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
             ms_phase[3] += elapsed(EV_X, EV_T);
             for (int k = 0; k < 4; ++k)
                 if (ccls[k]) {
-                    ms_kind[k] += elapsed(EV_S0 + k, EV_K0 + k);
+                    ms_kind[k] += multi ? elapsed(EV_S0 + k, EV_K0 + k) : elapsed(EV_F1, EV_J);
                     launches_kind[k] += 1;
                 }
             if (ccls[3]) {
                 // the path launches follow each other on ks[3]: path 0, path 2, path 1
-                if (gcnt[0]) { ms_path[0] += elapsed(EV_S0 + 3, EV_P0); launches_path[0] += 1; }
+                if (gcnt[0]) { ms_path[0] += elapsed(multi ? EV_S3 : EV_F1, EV_P0); launches_path[0] += 1; }
                 if (gcnt[1]) { ms_path[2] += elapsed(EV_P0, EV_P2); launches_path[2] += 1; }
-                if (gcnt[2]) { ms_path[1] += elapsed(EV_P2, EV_K0 + 3); launches_path[1] += 1; }
+                if (gcnt[2]) { ms_path[1] += elapsed(EV_P2, multi ? EV_K3 : EV_J); launches_path[1] += 1; }
             }
             launches_phase[0] += 1;
             launches_phase[1] += nl;
