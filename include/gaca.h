@@ -327,7 +327,7 @@ gaca_status gaca_apply(gaca_hmatrix *h, gaca_apply_mode mode, int32_t nrhs, cons
 /* Allocation-free apply, for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc).  Same arguments and
  * results as gaca_apply, computed with the VALU kernels of gaca_apply (no matrix-core path);
- * its workspace (tree-order copies of X and Y, the per-block z, T and y and their offsets)
+ * its workspace (tree-order copies of X and Y, z and its offsets; the limit also counts a T and y)
  * lives in a fixed 64 MiB scratch array per device instead of memory allocated per operator.
  * The call allocates nothing and frees nothing.  GACA_ERR_INVALID_ARG if the workspace of
  * this operator, mode, nrhs and dtype exceeds 64 MiB (it grows as L M nrhs); GACA_ERR_STATE
