@@ -1098,8 +1098,9 @@ static NearSeries near_series(const gaca_problem *p, int tier, bool &rest) {
     const double zfar = (std::fabs(S.c) + S.R) * (p->near_diam + p->near_h) * (kNearSeriesMax / 600.0);
     rest = !(std::max(z, zfar) <= kNearSeriesMax);
     // With fewer than eight frequencies the moments cost more than the points; a disc far from
-    // the origin for its size needs powers of c / R
-    if (p->f.L_eval >= 8 && S.R >= 1e-3 * std::fabs(S.c) && std::isfinite(S.R))
+    // the origin for its size needs powers of c / R, and 1 / R has to be a number (one frequency many
+    // times, zero among them)
+    if (p->f.L_eval >= 8 && S.R >= 1e-3 * std::fabs(S.c) && S.R >= 1e-290 && std::isfinite(S.R))
         S.K = z <= 2.0 ? 24 : z <= 3.5 ? 32 : 44;
     if (S.K == 0) rest = true;
     return S;
