@@ -1096,7 +1096,7 @@ static NearSeries near_series(const gaca_problem *p, int tier, bool &rest) {
     double z = S.R * p->near_h * (gal ? 4.0 / 3.0 : p->p1() ? 1.0 : 2.0 / 3.0);
     if (gal && tier >= 3) z = std::max(std::fabs(S.c), S.R) * p->near_h * (tier == 5 ? 1.0 : 2.0);
     const double zfar = (std::fabs(S.c) + S.R) * (p->near_diam + p->near_h) * (kNearSeriesMax / 600.0);
-    rest = !(std::max(z, zfar) <= kNearSeriesMax);
+    rest = !(std::max(z, zfar) * 1.001 <= kNearSeriesMax);   // the device's own rounding of a pair's bound
     // With fewer than eight frequencies the moments cost more than the points; a disc far from
     // the origin for its size needs powers of c / R, and 1 / R has to be a number (one frequency many
     // times, zero among them)

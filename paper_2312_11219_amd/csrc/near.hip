@@ -25,7 +25,7 @@ __global__ void __launch_bounds__(256)
     NearBlockDev B = blocks[pr.blk];
     const int64_t i = B.r0 + pr.i, j = B.c0 + pr.j;
     double ar[NF], ai[NF], rc;
-    if (S.K > 0 && gal_span<TIER>(g, S, i, j, rc) <= kNearSeriesMax) return;   // near_moments.hip
+    if (S.K > 0 && gal_span<TIER>(g, S, i, j, rc) <= kSeriesSafe) return;   // near_moments.hip
     gal_near_entry<NF>(g, q, f, i, j, TIER, l0, nl, ar, ai);
     const int64_t base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
 #pragma unroll
@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(256)
     NearBlockDev B = blocks[pr.blk];
     const int64_t i = B.r0 + pr.i, j = B.c0 + pr.j;
     double ar[NF], ai[NF], rc;
-    if (S.K > 0 && near_span(g, S, i, j, rc) <= kNearSeriesMax) return;   // near_moments.hip
+    if (S.K > 0 && near_span(g, S, i, j, rc) <= kSeriesSafe) return;   // near_moments.hip
     near_entry<KERNEL, NF>(g, q, f, i, j, TIER, l0, nl, ar, ai);
     const int64_t base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
 #pragma unroll
@@ -162,7 +162,7 @@ __global__ void __launch_bounds__(256)
     NearBlockDev B = blocks[pr.blk];
     const int64_t i = B.r0 + pr.i, j = B.c0 + pr.j;
     double ar[NF], ai[NF], rc;
-    if (S.K > 0 && p1_span(g, S, i, j, rc) <= kNearSeriesMax) return;   // near_moments.hip
+    if (S.K > 0 && p1_span(g, S, i, j, rc) <= kSeriesSafe) return;   // near_moments.hip
     p1_entry<NF>(g, q, f, i, j, false, l0, nl, ar, ai);
     const int64_t base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
 #pragma unroll

@@ -21,6 +21,11 @@ __device__ __forceinline__ double tri_radius(const GeoDev &g, int64_t t) {
                 dist3(g.cx[t], g.cy[t], g.cz[t], cx, cy, cz));
 }
 
+// Two kernels may round a pair's bound differently: the series takes pairs up to kNearSeriesMax, the
+// kernels that visit the points at every frequency leave out those safely below it.  What both
+// write is the same entry.
+constexpr double kSeriesSafe = kNearSeriesMax * (1.0 - 1e-9);
+
 // Argument of the series' bound; the exponentials at r_c and over the span stay far from the ends
 // of the range of doubles.
 __device__ __forceinline__ double span_bound(const NearSeries &S, double rc, double half) {
