@@ -19,7 +19,7 @@ LIB = os.path.join(HERE, "libgaca.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-HOST_SRC = ["host.cpp", "lib.cpp", "gcq_host.cpp"]
+HOST_SRC = ["host.cpp", "lib.cpp", "gcq_host.cpp", "near_series.cpp"]
 HIP_SRC = ["near.hip", "near_moments.hip", "near_gp1.hip", "far_aca.hip", "far_aca_reg.hip", "apply.hip", "apply_mfma.hip", "gcq.hip",
            "far_recompress.hip", "near_aca.hip"]
 COMMON = ["-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I" + CSRC,

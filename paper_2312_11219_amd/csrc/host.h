@@ -55,6 +55,19 @@ int32_t galerkin_tier(const HostMesh &mesh, int64_t i, int64_t j);
 constexpr int kNumTiers = 6;          // pair classes (collocation uses the first 4)
 constexpr int kGalerkinNTheta = 16;   // Gauss points per angular sector (coincident pairs)
 
+// Chebyshev series of a near-field class (near_series.cpp) for the n frequencies evaluated.  rest: some
+// pairs may be beyond the series (all of them if S.K is 0).  The pointers in S are the caller's to set.
+struct SeriesTables {
+    NearSeries S{};
+    bool rest = true;
+    std::vector<int32_t> order;
+    std::vector<double2> coef;   // [position in order][term]
+    // regular pairs: half-spans up to reach, middle distances up to rc_max; bands up to |Re s - c| half = band
+    void build(double band, double reach, double rc_max, const double *re, const double *im, int n);
+    // radial integrals of touching Galerkin pairs (edge, vertex, coincident), distances up to reach
+    static void build_touching(double reach, const double *re, const double *im, int n, SeriesTables (&T)[3]);
+};
+
 // gCQ integration points and weights (App. A); throws Error on invalid input.
 void gcq_contour(int stages, const double *rk_A, double dt_min, double dt_max, int n_q,
                  double *s_re, double *s_im, double *w_re, double *w_im);

@@ -79,13 +79,21 @@ struct FreqDev {
     const double *re, *im;
 };
 
-// Power series of the near field in the frequency: the frequencies lie in |s - c| <= R, c real;
-// K terms (0: none, every pair is evaluated at every frequency)
+// Chebyshev series of the near field (near_moments.hip): K terms (0: every pair is evaluated point by
+// point at every frequency), the frequencies of band b at order[first[b] .. first[b + 1]) about the real
+// centre c[b], for pairs with half-span up to half (touching pairs: distances up to half) and middle
+// distance up to rmax; coefficients [position in order][term] and [term][position]
+constexpr int kNearBands = 5;
 struct NearSeries {
-    double c, R;
-    int K;
+    int32_t K, nband;
+    double half, rmax;
+    double c[kNearBands];
+    int32_t first[kNearBands + 1];
+    const int32_t *order;
+    const double2 *by_freq, *by_term;
 };
-constexpr double kNearSeriesMax = 6.0;   // largest R delta (touching pairs: max(|c|, R) rho)
+constexpr double kNearSeriesMax = 6.0;   // largest |s - c| half (touching pairs: |s| half / 2)
+constexpr double kNearBandFar = 2.0, kNearBand = 1.25;   // largest |Re s - c[b]| half (near_moments.hip)
 
 enum Tier : int32_t { TIER_FAR6 = 0, TIER_MID4 = 1, TIER_NEAR8 = 2, TIER_SELF = 3 };
 

@@ -80,7 +80,7 @@ void launch_near_gp1_pairs(int op, const GeoDev &g, const QuadDev &q, const Freq
 
 // Near field: every pair of one tier, all frequencies, FP64 compute, stored as double2
 // (out64) or float2 (out32).
-// Near field from moments of the quadrature points (S.K > 0): the pairs within the series' bound.
+// Near field from moments of the quadrature points (S.K > 0): the pairs that the series covers.
 // launch_near, launch_near_galerkin and launch_near_p1 with the same S take the others.
 void launch_near_series(int kernel, int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
                         const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks, double2 *out64,
@@ -88,7 +88,8 @@ void launch_near_series(int kernel, int tier, const GeoDev &g, const QuadDev &q,
 void launch_near_series_galerkin(int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
                                  const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks, double2 *out64,
                                  float2 *out32, hipStream_t st);
-void launch_near_series_p1(const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
+// tier 0: pairs that take the 6-point rule on every triangle
+void launch_near_series_p1(int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
                            const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks, double2 *out64,
                            hipStream_t st);
 

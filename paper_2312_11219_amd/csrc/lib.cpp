@@ -420,6 +420,7 @@ struct gaca_problem {
     std::vector<int32_t> pptr, ptri, ploc;
     std::vector<double> patch_prefix;    // prefix sums of the patch sizes in tree order
     double p1_near_points = 0.0;         // quadrature points of the near field per frequency
+    int64_t p1_far_pairs = 0;            // near pairs with the 6-point rule on every triangle (the first ones)
     DevBuf d_p1i;
     // Galerkin P1: the triangle pairs of the near field and the buffer of their integrals (kept
     // for the problem's builds; nfc frequencies at a time, 0: no pair list, entry by entry)
@@ -431,9 +432,14 @@ struct gaca_problem {
     int32_t L = 0;
     std::vector<double> s_re, s_im;
     bool mirror = false;
-    // near field as a power series in the frequency: disc of the frequencies, longest edge, diameter
-    NearSeries series{0.0, 0.0, 0};
-    double near_h = 0.0, near_diam = 0.0;
+    // Chebyshev series of the near field's classes: pairs with 6-point rules (tier 0, P1 pairs with these only),
+    // other regular pairs, then the touching Galerkin tiers; rest: some pairs are left to the evaluation at
+    // every frequency
+    struct Series {
+        NearSeries S{};
+        bool rest = true;
+    } series[5];
+    DevBuf d_series;
     int64_t M = 0;
     std::vector<int64_t> inv_perm;
     // device geometry / tables
@@ -917,11 +923,14 @@ static void upload_problem_p1(gaca_problem *p) {
     g.dvid = g.tv2 + T;
     upload_quad(p);
     p->d_perm.upload(ctx, p->tree.perm);
-    // near blocks: one pair list; the host counts the quadrature points of every pair with
-    // the device's per-triangle rule (algorithmic work of the near field)
+    // near blocks: one pair list, the pairs that take the 6-point rule on every triangle first; the
+    // host counts the quadrature points of every pair with the device's per-triangle rule
+    // (algorithmic work of the near field)
     p->nblocks.clear();
     int64_t off = 0;
-    std::vector<NearPair> pairs;
+    size_t nfirst = 0, nlast = 0;   // pairs in place from the front, from the end
+    for (const auto &nb : p->part.near) nlast += (size_t)(nb[1] * nb[3]);
+    std::vector<NearPair> pairs(nlast);
     const double nm2 = (double)p->opt.quad_mid * p->opt.quad_mid;
     const double nn2 = (double)p->opt.quad_near * p->opt.quad_near;
     double pts = 0.0;
@@ -936,13 +945,15 @@ static void upload_problem_p1(gaca_problem *p) {
             const int64_t vi = p->tree.perm[nb[0] + i];
             const double *x = &m.xyz[3 * vi];
             for (int64_t j = 0; j < nb[3]; ++j) {
-                pairs.push_back(NearPair{(int32_t)b, (int16_t)i, (int16_t)j});
+                const NearPair np{(int32_t)b, (int16_t)i, (int16_t)j};
                 const int64_t tj = nb[2] + j;
                 if (p->scheme == GACA_GALERKIN_P1) {
+                    pairs[nfirst++] = np;
                     // estimate: 36 points per triangle pair of the two patches
                     pts += 36.0 * (p->pptr[nb[0] + i + 1] - p->pptr[nb[0] + i]) * (p->pptr[tj + 1] - p->pptr[tj]);
                     continue;
                 }
+                double least = INFINITY;
                 for (int32_t e = p->pptr[tj]; e < p->pptr[tj + 1]; ++e) {
                     const int64_t t = p->ptri[e];
                     if (m.tri[3 * t] == vi || m.tri[3 * t + 1] == vi || m.tri[3 * t + 2] == vi) continue;
@@ -950,12 +961,15 @@ static void upload_problem_p1(gaca_problem *p) {
                     for (int k = 0; k < 3; ++k) dv[k] = x[k] - m.cen[3 * t + k];
                     const double qd = std::sqrt(dv[0] * dv[0] + dv[1] * dv[1] + dv[2] * dv[2]) / m.hmax[t];
                     pts += qd >= 4.0 ? 6.0 : (qd >= 2.0 ? nm2 : nn2);
+                    least = std::min(least, qd);
                 }
+                pairs[least >= 4.0 ? nfirst++ : --nlast] = np;
             }
         }
     }
     p->near_elems = off;
     p->p1_near_points = pts;
+    p->p1_far_pairs = (int64_t)nfirst;
     p->d_nblocks.upload(ctx, p->nblocks);
     for (int t = 0; t < kNumTiers; ++t) {
         p->npairs[t] = t == 0 ? (int64_t)pairs.size() : 0;
@@ -1067,43 +1081,70 @@ static void upload_freq(gaca_problem *p) {
     p->f.L_eval = p->mirror ? (p->L + 1) / 2 : p->L;
 }
 
-// Disc of the frequencies and extents of the mesh for near_series.
-static void near_extents(gaca_problem *p) {
-    double lo = INFINITY, hi = -INFINITY;
-    for (int l = 0; l < p->L; ++l) {
-        lo = std::min(lo, p->s_re[l]);
-        hi = std::max(hi, p->s_re[l]);
+static void upload_series(gaca_problem *p) {
+    const HostMesh &mesh = p->mesh;
+    const bool gal = p->scheme == GACA_GALERKIN_P0;
+    if (p->scheme == GACA_GALERKIN_P1) return;
+    double h = 0.0, rad = 0.0, lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (int64_t e = 0; e < mesh.M; ++e) {
+        h = std::max(h, mesh.hmax[e]);
+        for (int v = 0; v < 9; v += 3) {
+            const double *x = &mesh.vert[9 * e + v], *c = &mesh.cen[3 * e];
+            rad = std::max(rad, std::sqrt((x[0] - c[0]) * (x[0] - c[0]) + (x[1] - c[1]) * (x[1] - c[1]) +
+                                          (x[2] - c[2]) * (x[2] - c[2])));
+            for (int k = 0; k < 3; ++k) {
+                lo[k] = std::min(lo[k], x[k]);
+                hi[k] = std::max(hi[k], x[k]);
+            }
+        }
     }
-    NearSeries &S = p->series;
-    S = NearSeries{0.5 * (lo + hi), 0.0, 0};
-    for (int l = 0; l < p->L; ++l) S.R = std::max(S.R, std::hypot(p->s_re[l] - S.c, p->s_im[l]));
-    for (double h : p->mesh.hmax) p->near_h = std::max(p->near_h, h);
-    double a[3] = {INFINITY, INFINITY, INFINITY}, b[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (size_t v = 0; v < p->mesh.vert.size(); ++v) {
-        a[v % 3] = std::min(a[v % 3], p->mesh.vert[v]);
-        b[v % 3] = std::max(b[v % 3], p->mesh.vert[v]);
+    // half-spans: the radius of the column triangle, of both (Galerkin), of a vertex patch (P1);
+    // distances of touching pairs: up to the longest edges of both
+    const double diam = std::hypot(hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2]) + h;
+    constexpr int NC = 5;
+    SeriesTables T[NC], touch[3];
+    for (int c = 0; c < 2; ++c)
+        T[c].build(c == 0 ? kNearBandFar : kNearBand, gal ? 2.0 * rad : p->p1() ? h : rad, diam, p->s_re.data(),
+                   p->s_im.data(), p->f.L_eval);
+    if (gal) {
+        SeriesTables::build_touching(2.0 * h, p->s_re.data(), p->s_im.data(), p->f.L_eval, touch);
+        for (int c = 0; c < 3; ++c) T[2 + c] = std::move(touch[c]);
     }
-    p->near_diam = std::hypot(b[0] - a[0], b[1] - a[1], b[2] - a[2]);
+    // one buffer: the coefficients in both orders, then the order of the frequencies
+    std::vector<double2> all;
+    size_t at[NC];
+    for (int c = 0; c < NC; ++c) {
+        at[c] = all.size();
+        const int K = T[c].S.K, nf = (int)T[c].order.size();
+        all.insert(all.end(), T[c].coef.begin(), T[c].coef.end());
+        for (int k = 0; k < K; ++k)
+            for (int f = 0; f < nf; ++f) all.push_back(T[c].coef[(size_t)f * K + k]);
+        const size_t n = all.size(), words = sizeof(double2) / sizeof(int32_t);
+        all.resize(n + (T[c].order.size() + words - 1) / words);
+        if (!T[c].order.empty()) std::memcpy(&all[n], T[c].order.data(), T[c].order.size() * sizeof(int32_t));
+    }
+    if (all.empty()) return;
+    try {
+        p->d_series.upload(p->ctx, all);
+    } catch (const Error &) {   // no memory: every pair at every frequency
+        p->d_series.release();
+        return;
+    }
+    for (int c = 0; c < NC; ++c) {
+        const size_t n = T[c].coef.size();
+        if (n == 0) continue;
+        auto &P = p->series[c];
+        P.rest = T[c].rest;
+        P.S = T[c].S;
+        P.S.by_freq = p->d_series.as<double2>() + at[c];
+        P.S.by_term = P.S.by_freq + n;
+        P.S.order = reinterpret_cast<const int32_t *>(P.S.by_term + n);
+    }
 }
 
-// Series of a near-field class: K = 0 if its pairs are evaluated at every frequency; rest: some may
-// be beyond the series' bound and are left to those kernels.
-static NearSeries near_series(const gaca_problem *p, int tier, bool &rest) {
-    NearSeries S = p->series;
-    // bound over the problem's pairs: a triangle lies within 2/3 of its longest edge of its
-    // centroid, a P1 patch within its longest edge of the vertex
-    const bool gal = p->scheme == GACA_GALERKIN_P0;
-    double z = S.R * p->near_h * (gal ? 4.0 / 3.0 : p->p1() ? 1.0 : 2.0 / 3.0);
-    if (gal && tier >= 3) z = std::max(std::fabs(S.c), S.R) * p->near_h * (tier == 5 ? 1.0 : 2.0);
-    const double zfar = (std::fabs(S.c) + S.R) * (p->near_diam + p->near_h) * (kNearSeriesMax / 600.0);
-    rest = !(std::max(z, zfar) * 1.001 <= kNearSeriesMax);   // the device's own rounding of a pair's bound
-    // With fewer than eight frequencies the moments cost more than the points; a disc far from
-    // the origin for its size needs powers of c / R, and 1 / R has to be a number (one frequency many
-    // times, zero among them)
-    if (p->f.L_eval >= 8 && S.R >= 1e-3 * std::fabs(S.c) && S.R >= 1e-290 && std::isfinite(S.R))
-        S.K = z <= 2.0 ? 24 : z <= 3.5 ? 32 : 44;
-    if (S.K == 0) rest = true;
-    return S;
+// The series of a near-field tier: K = 0 if all of its pairs are evaluated at every frequency.
+static const gaca_problem::Series &near_series(const gaca_problem *p, int tier) {
+    return p->series[p->scheme == GACA_GALERKIN_P0 && tier >= 3 ? tier - 1 : tier == 0 ? 0 : 1];
 }
 
 gaca_status gaca_problem_create(gaca_context *ctx, const double *xyz, int64_t nv,
@@ -1159,7 +1200,7 @@ gaca_status gaca_problem_create(gaca_context *ctx, const double *xyz, int64_t nv
         GACA_HIP_CHECK(hipSetDevice(ctx->device));
         upload_problem(p.get());
         upload_freq(p.get());
-        near_extents(p.get());
+        upload_series(p.get());
         if (scheme == GACA_GALERKIN_P1) upload_gp1_pairs(p.get());
         *out = p.release();
     });
@@ -2360,14 +2401,16 @@ static bool build_ops(gaca_problem *p, const std::vector<gaca_kernel> &kernels,
             double2 *n64 = mixed ? nullptr : h->d_near.as<double2>();
             float2 *n32 = mixed ? h->d_near.as<float2>() : nullptr;
             if (p->scheme == GACA_COLLOCATION_P1) {
-                bool rest;
-                const NearSeries S = near_series(p, 0, rest);
-                if (S.K > 0)
-                    launch_near_series_p1(p->g, p->q, p->f, S, p->d_pairs[0].as<NearPair>(), p->npairs[0],
-                                          p->d_nblocks.as<NearBlockDev>(), n64, st);
-                if (rest)
-                    launch_near_p1(p->g, p->q, p->f, S, p->d_pairs[0].as<NearPair>(), p->npairs[0],
-                                   p->d_nblocks.as<NearBlockDev>(), n64, st);
+                const NearBlockDev *nb = p->d_nblocks.as<NearBlockDev>();
+                const NearPair *pairs = p->d_pairs[0].as<NearPair>();
+                int64_t cnt = p->p1_far_pairs;
+                for (int t = 0; t < 2; ++t) {   // 6-point rules on every triangle, others
+                    const gaca_problem::Series &S = near_series(p, t);
+                    if (S.S.K > 0) launch_near_series_p1(t, p->g, p->q, p->f, S.S, pairs, cnt, nb, n64, st);
+                    if (S.rest) launch_near_p1(p->g, p->q, p->f, S.S, pairs, cnt, nb, n64, st);
+                    pairs += cnt;
+                    cnt = p->npairs[0] - cnt;
+                }
             }
             if (p->scheme == GACA_GALERKIN_P1) {
                 const int op = kernels[w] == GACA_HYP ? 0 : 1;
@@ -2391,8 +2434,8 @@ static bool build_ops(gaca_problem *p, const std::vector<gaca_kernel> &kernels,
                 const NearPair *pairs = p->d_pairs[t].as<NearPair>();
                 const NearBlockDev *nb = p->d_nblocks.as<NearBlockDev>();
                 if (!gal && t > 3) continue;
-                bool rest;
-                NearSeries S = near_series(p, t, rest);
+                bool rest = near_series(p, t).rest;
+                NearSeries S = near_series(p, t).S;
                 if (!gal && t == TIER_SELF && kernels[w] == 1) {   // zeros
                     S.K = 0;
                     rest = true;

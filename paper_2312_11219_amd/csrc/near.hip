@@ -24,8 +24,12 @@ __global__ void __launch_bounds__(256)
     NearPair pr = pairs[p];
     NearBlockDev B = blocks[pr.blk];
     const int64_t i = B.r0 + pr.i, j = B.c0 + pr.j;
-    double ar[NF], ai[NF], rc;
-    if (S.K > 0 && gal_span<TIER>(g, S, i, j, rc) <= kSeriesSafe) return;   // near_moments.hip
+    double ar[NF], ai[NF];
+    if (S.K > 0) {
+        double rc, half;
+        gal_span<TIER>(g, i, j, rc, half);
+        if (series_covers(S, rc, half, kSeriesSafe)) return;   // near_moments.hip
+    }
     gal_near_entry<NF>(g, q, f, i, j, TIER, l0, nl, ar, ai);
     const int64_t base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
 #pragma unroll
@@ -93,8 +97,12 @@ __global__ void __launch_bounds__(256)
     NearPair pr = pairs[p];
     NearBlockDev B = blocks[pr.blk];
     const int64_t i = B.r0 + pr.i, j = B.c0 + pr.j;
-    double ar[NF], ai[NF], rc;
-    if (S.K > 0 && near_span(g, S, i, j, rc) <= kSeriesSafe) return;   // near_moments.hip
+    double ar[NF], ai[NF];
+    if (S.K > 0) {
+        double rc, half;
+        near_span(g, i, j, rc, half);
+        if (series_covers(S, rc, half, kSeriesSafe)) return;   // near_moments.hip
+    }
     near_entry<KERNEL, NF>(g, q, f, i, j, TIER, l0, nl, ar, ai);
     const int64_t base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
 #pragma unroll
@@ -161,8 +169,12 @@ __global__ void __launch_bounds__(256)
     NearPair pr = pairs[p];
     NearBlockDev B = blocks[pr.blk];
     const int64_t i = B.r0 + pr.i, j = B.c0 + pr.j;
-    double ar[NF], ai[NF], rc;
-    if (S.K > 0 && p1_span(g, S, i, j, rc) <= kSeriesSafe) return;   // near_moments.hip
+    double ar[NF], ai[NF];
+    if (S.K > 0) {
+        double rc, half;
+        p1_span(g, i, j, rc, half);
+        if (series_covers(S, rc, half, kSeriesSafe)) return;   // near_moments.hip
+    }
     p1_entry<NF>(g, q, f, i, j, false, l0, nl, ar, ai);
     const int64_t base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
 #pragma unroll

@@ -1,30 +1,35 @@
 // Near field of every frequency from moments of the quadrature points.
 //
-// An entry is sum_q w_q k(r_q) e^{-s r_q} over the points of its rule.  With the frequencies in the
-// disc |s - c| <= R (c real) and the distances in r_c +- delta, R delta <= 6, the sum is a power
-// series in (s - c) / R,
-//   e^{-s r_c} sum_m (-(s - c) / R)^m M_m,   M_m = sum_q w_q k(r_q) e^{-c (r_q - r_c)} tau_q^m / m!,
-//   tau_q = R (r_q - r_c),
-// cut after K terms where the rest is below the rounding of the sum (R delta up to 2: 24 terms,
-// 2^24 / 24! = 3e-17; 3.5: 32, 1e-18; 6: 44, 6e-21).  The points are visited once, with one real exponential each, instead of once
-// per frequency with e^x, sin and cos; a frequency then costs K complex steps.  The double layer's
-// factor 1 + s r = (1 + s r_c) + s (r - r_c) takes the derivative of the series along:
-//   sum_q (r_q - r_c) ... = P'(u) / R,  u = -(s - c) / R.
-// Touching and coincident Galerkin pairs carry exact radial integrals of e^{-s rho u},
-//   phi2: u^2,  phie: u - u^2,  psi: (1 - u)^2,   0 <= u <= 1;
-// with J_n(x) = int u^n e^{-x u} du their moments are combinations of
-// S_m^p = sum_q w_q tau_q^m / m! J_{m+p}(c rho_q), p = 0, 1, 2, and J_n = (x J_{n+1} + e^{-x}) / (n + 1) gives
-//   S_m^p = ((c / R) (m + 1) S_{m+1}^p + B_m) / (m + p + 1)
-// from the moments B_m = sum_q w_q e^{-c rho_q} tau_q^m / m!, tau = R rho (max(|c|, R) rho <= 6: all
-// sums are of one sign and the start from 0 at m = K is below the rounding).
+// An entry is sum_q w_q k(r_q) e^{-s r_q} over the points of its rule (double layer: with the factor
+// 1 + s r_q).  With the distances in r_c +- delta, delta <= Delta (the class's largest), and the
+// frequencies in bands of real parts about real centres c,
+//   e^{-s r} = e^{-s r_c} e^{-c (r - r_c)} sum_k a_k(s) T_k(x),  x = (r - r_c) / Delta,
+// the Chebyshev series of e^{-z x}, z = (s - c) Delta (a_k: modified Bessel functions of z), cut where
+// the rest is below the rounding of the sum (near_series.cpp: 16 terms for |z| <= 1.1, 20 for 2.2, 24 for
+// 3.7, 30 for 6.2).  The points are visited once per band, for
+//   M_k = sum_q w_q k(r_q) e^{-c (r_q - r_c)} T_k(x_q)
+// and, in the double layer, the same with another factor r_q; a frequency then costs one real times
+// complex product a term.  Touching and coincident Galerkin pairs carry exact radial integrals phi(s rho),
+// which fall off as powers only: the Chebyshev series of phi(s rho) on 0 <= rho <= Delta, one band, no
+// exponential.
 //
-// What bounds it: the moments' multiply-adds (FP64 VALU, two per moment and point) where a rule has
-// many points, the writes of the entries and the steps per frequency where it has few.  G lanes
-// share a pair, first its points, then its frequencies.  Near field of a build, every point at every
-// frequency -> moments: Galerkin P0 (3072-triangle L-shape, L = 96) 82 -> 5.6 ms; P1 double layer
-// (4802-vertex sphere, L = 128) 49 -> 10 ms; collocation (9408-triangle sphere, L = 128) 17.5 ->
-// 9.1 ms, of which the writes of its 18 GB take 4.  Pairs beyond the bound (few elements per
-// wavelength) are left to the kernels that visit the points at every frequency.
+// Rounding: sum |a_k| is the few that it is for imaginary z, times up to e^{|Re z|}, so the bands keep
+// |Re z| <= 1.25, and <= 2 for the 6-point rules of distant pairs (whose own rounding, of s r at every
+// point, is larger).  s r_c is formed with its remainder, and the two parts of the double layer have
+// positive weights.  Against 80-bit arithmetic on random pairs, R Delta up to 6 (R: radius of the
+// frequencies), largest error of an entry relative to it, in brackets point by point: 6 points, far 4.2e-15
+// (1.4e-14); 16 points 1.8e-15 (6.7e-15); 64 points, close 1.7e-15 (1.5e-15); touching pairs up to
+// |s| rho = 12 5.5e-15 (5.5e-15).  One power series in s - c for all frequencies, whose terms
+// exceed its sum by up to e^{2 R delta}, had 4e-13.
+//
+// What bounds it: the moments' multiply-adds (FP64 VALU, two or three per moment, point and band) where a
+// rule has many points, the writes of the entries and the steps per frequency where it has few.  G lanes
+// share a pair and band, first its points, then its frequencies.  Near field of a build beside the far
+// field, every point at every frequency -> moments: Galerkin P0 (3072-triangle L-shape, L = 96) 82 -> 11 ms;
+// P1 double layer (4802-vertex sphere, L = 128) 49 -> 9.1 ms; collocation (9408-triangle sphere, L = 128)
+// 17.5 -> 10.8 ms, of which the writes of its 18 GB take 4.  (The power series took 6.2, 6.2 and 10.7.)
+// Pairs beyond the bound (few elements per wavelength) are left to the kernels that visit the points at
+// every frequency.
 #include <hip/hip_runtime.h>
 
 #include "device_util.h"
@@ -37,18 +42,6 @@ namespace gaca {
 
 namespace {
 
-template <int K>
-struct InvFact {
-    double v[K];
-    constexpr InvFact() : v{} {
-        double f = 1.0;
-        for (int k = 0; k < K; ++k) {
-            if (k > 0) f /= k;
-            v[k] = f;
-        }
-    }
-};
-
 // sum over G adjacent lanes (a power of two up to 16), in every one of them
 template <int G>
 __device__ __forceinline__ double group_sum(double v) {
@@ -59,73 +52,80 @@ __device__ __forceinline__ double group_sum(double v) {
     return v;
 }
 
-template <int K>
+// M_k and, with D, the same weighted by r
+template <int K, bool D>
 struct Moments {
-    double m[K];
+    double m[K], n[D ? K : 1];
     __device__ __forceinline__ void zero() {
 #pragma unroll
-        for (int k = 0; k < K; ++k) m[k] = 0.0;
+        for (int k = 0; k < K; ++k) {
+            m[k] = 0.0;
+            if (D) n[k] = 0.0;
+        }
     }
-    __device__ __forceinline__ void add(double tau, double w) {
-        double t = w;
+    __device__ __forceinline__ void add(double x, double r, double w) {
+        const double x2 = 2.0 * x;
+        double t0 = w, t1 = w * x;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            m[k] += t;
-            t *= tau;
+            m[k] += t0;
+            if (D) n[k] = fma(r, t0, n[k]);
+            const double t2 = fma(x2, t1, -t0);
+            t0 = t1;
+            t1 = t2;
         }
     }
-    // the lanes' sums together, over k!
+    // the lanes' sums together
     template <int G>
     __device__ __forceinline__ void finish() {
-        constexpr InvFact<K> F;
 #pragma unroll
-        for (int k = 0; k < K; ++k) m[k] = group_sum<G>(m[k]) * F.v[k];
-    }
-    // B_m -> S_m^2 (WHAT 0), S_m^1 - S_m^2 (1), S_m^0 - 2 S_m^1 + S_m^2 (2)
-    template <int WHAT>
-    __device__ __forceinline__ void radial(double cr) {
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-#pragma unroll
-        for (int k = K - 1; k >= 0; --k) {
-            const double b = m[k], a = cr * (k + 1);
-            s2 = fma(a, s2, b) * (1.0 / (k + 3));
-            if (WHAT > 0) s1 = fma(a, s1, b) * (1.0 / (k + 2));
-            if (WHAT > 1) s0 = fma(a, s0, b) * (1.0 / (k + 1));
-            m[k] = WHAT == 0 ? s2 : WHAT == 1 ? s1 - s2 : (s0 - s1) - (s1 - s2);
+        for (int k = 0; k < K; ++k) {
+            m[k] = group_sum<G>(m[k]);
+            if (D) n[k] = group_sum<G>(n[k]);
         }
     }
-    // P(u) (and P'(u))
-    template <bool D>
-    __device__ __forceinline__ void eval(double ur, double ui, double2 &P, double2 &dP) const {
-        double pr = m[K - 1], pi = 0.0, dr = 0.0, di = 0.0;
+    // sum_k a_k M_k (+ s sum_k a_k N_k), the terms at a[k step].  ONE: every lane of the wave takes this
+    // frequency, and the table is read as constant memory, by scalar loads
+    template <bool ONE>
+    __device__ __forceinline__ double2 eval(const double2 *a, int step, double sr, double si) const {
+        const auto *ac = (const __attribute__((address_space(4))) double *)a;
+        double pr = 0.0, pi = 0.0, nr = 0.0, ni = 0.0;
 #pragma unroll
-        for (int k = K - 2; k >= 0; --k) {
+        for (int k = 0; k < K; ++k) {
+            const double cr = ONE ? ac[2 * k * step] : a[k * step].x, ci = ONE ? ac[2 * k * step + 1] : a[k * step].y;
+            pr = fma(cr, m[k], pr);
+            pi = fma(ci, m[k], pi);
             if (D) {
-                const double nr = fma(ur, dr, fma(-ui, di, pr));
-                di = fma(ur, di, fma(ui, dr, pi));
-                dr = nr;
+                nr = fma(cr, n[k], nr);
+                ni = fma(ci, n[k], ni);
             }
-            const double nr = fma(ur, pr, fma(-ui, pi, m[k]));
-            pi = fma(ur, pi, ui * pr);
-            pr = nr;
+            if (ONE && k % 6 == 5) __builtin_amdgcn_sched_barrier(0);   // six terms in flight: more cost registers
         }
-        P = make_double2(pr, pi);
-        dP = make_double2(dr, di);
+        if (D) {
+            pr += sr * nr - si * ni;
+            pi += sr * ni + si * nr;
+        }
+        return make_double2(pr, pi);
     }
 };
 
-template <int KERNEL, int K>
-__device__ __forceinline__ void add_point(Moments<K> &M, const NearSeries &S, double rc, double r, double ir, double w) {
-    const double dr = r - rc;
-    M.add(S.R * dr, w * kInvFourPi * (KERNEL == 0 ? ir : ir * ir * ir) * fm::exp(-S.c * dr));
+// the band's centre and the pair's middle distance; 1 / Delta (touching pairs: 2 / Delta)
+struct Span {
+    double c, rc, scale;
+};
+
+template <int K, bool D>
+__device__ __forceinline__ void add_point(Moments<K, D> &M, const Span &S, double r, double ir, double w) {
+    const double dr = r - S.rc;
+    M.add(dr * S.scale, r, w * kInvFourPi * (D ? ir * ir * ir : ir) * fm::exp(-S.c * dr));
 }
 
 // points sub, sub + G, ... of the collapsed n x n rule on (a, b, c) seen from x; lam < 0, or the
 // barycentric coordinate that weighs them
-template <int KERNEL, int K, int G>
-__device__ __forceinline__ void add_collapsed(Moments<K> &M, const NearSeries &S, double rc, const double *x,
-                                              const double *a, const double *b, const double *c, int n,
-                                              const double *gt, double wscale, int sub, int lam = -1) {
+template <int G, int K, bool D>
+__device__ __forceinline__ void add_collapsed(Moments<K, D> &M, const Span &S, const double *x, const double *a,
+                                              const double *b, const double *c, int n, const double *gt,
+                                              double wscale, int sub, int lam = -1) {
     const double e1x = b[0] - a[0], e1y = b[1] - a[1], e1z = b[2] - a[2];
     const double e2x = c[0] - b[0], e2y = c[1] - b[1], e2z = c[2] - b[2];
     const double nx = e1y * e2z - e1z * e2y, ny = e1z * e2x - e1x * e2z, nz = e1x * e2y - e1y * e2x;
@@ -137,20 +137,20 @@ __device__ __forceinline__ void add_collapsed(Moments<K> &M, const NearSeries &S
         if (lam >= 0) w *= lam == 0 ? 1.0 - u : (lam == 1 ? u - uv : uv);
         const double r = dist3_inv(x[0], x[1], x[2], a[0] + u * e1x + uv * e2x, a[1] + u * e1y + uv * e2y,
                                    a[2] + u * e1z + uv * e2z, ir);
-        add_point<KERNEL, K>(M, S, rc, r, ir, w);
+        add_point(M, S, r, ir, w);
     }
 }
 
 // w / (4 pi rho) at the end of the radial integral along d
 template <int K>
-__device__ __forceinline__ void add_radial(Moments<K> &M, const NearSeries &S, const double *d, double w) {
+__device__ __forceinline__ void add_radial(Moments<K, false> &M, const Span &S, const double *d, double w) {
     const double rho = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-    M.add(S.R * rho, w / (kFourPi * rho) * fm::exp(-S.c * rho));
+    M.add(fma(rho, S.scale, -1.0), 0.0, w / (kFourPi * rho));
 }
 
-template <int TIER, int K, int G>
-__device__ __forceinline__ void gal_moments(Moments<K> &M, const GeoDev &g, const QuadDev &q, const NearSeries &S,
-                                            double rc, int64_t i, int64_t j, int sub) {
+template <int TIER, int G, int K>
+__device__ __forceinline__ void gal_moments(Moments<K, false> &M, const GeoDev &g, const QuadDev &q, const Span &S,
+                                            int64_t i, int64_t j, int sub) {
     const double aj[3] = {g.ax[j], g.ay[j], g.az[j]}, bj[3] = {g.bx[j], g.by[j], g.bz[j]},
                  cj[3] = {g.cx[j], g.cy[j], g.cz[j]};
     const double ai[3] = {g.ax[i], g.ay[i], g.az[i]}, bi[3] = {g.bx[i], g.by[i], g.bz[i]},
@@ -162,7 +162,7 @@ __device__ __forceinline__ void gal_moments(Moments<K> &M, const GeoDev &g, cons
             double ir;
             const double r = dist3_inv(g.q6x[pi * T + i], g.q6y[pi * T + i], g.q6z[pi * T + i], g.q6x[pj * T + j],
                                        g.q6y[pj * T + j], g.q6z[pj * T + j], ir);
-            add_point<0, K>(M, S, rc, r, ir, g.q6w[pi * T + i] * g.q6w[pj * T + j]);
+            add_point(M, S, r, ir, g.q6w[pi * T + i] * g.q6w[pj * T + j]);
         }
     } else if constexpr (TIER == GT_MID || TIER == GT_NEAR) {
         const int no = TIER == GT_MID ? q.n4 : q.ng;
@@ -178,13 +178,13 @@ __device__ __forceinline__ void gal_moments(Moments<K> &M, const GeoDev &g, cons
             const double u = go[2 * iu], uv = u * go[2 * iv], wx = go[2 * iu + 1] * go[2 * iv + 1] * u * ws;
             const double x[3] = {ai[0] + u * e1x + uv * e2x, ai[1] + u * e1y + uv * e2y, ai[2] + u * e1z + uv * e2z};
             if constexpr (TIER == GT_MID) {
-                add_collapsed<0, K, 1>(M, S, rc, x, aj, bj, cj, q.n4, q.g4, wx, 0);
+                add_collapsed<1>(M, S, x, aj, bj, cj, q.n4, q.g4, wx, 0);
             } else {
                 double p[3];
                 closest_on_triangle(x, aj, bj, cj, p);
                 const double *V1 = s == 0 ? bj : (s == 1 ? cj : aj), *V2 = s == 0 ? cj : (s == 1 ? aj : bj);
                 const double p1[3] = {V1[0], V1[1], V1[2]}, p2[3] = {V2[0], V2[1], V2[2]};
-                add_collapsed<0, K, 1>(M, S, rc, x, p, p1, p2, q.ng, q.gg, wx, 0);
+                add_collapsed<1>(M, S, x, p, p1, p2, q.ng, q.gg, wx, 0);
             }
         }
     } else if constexpr (TIER == GT_COINC) {
@@ -231,7 +231,7 @@ __device__ __forceinline__ void gal_moments(Moments<K> &M, const GeoDev &g, cons
                 for (int k = 0; k < 3; ++k) gsum += fmax(0.0, Gx[k] * cs + Gy[k] * sn);
                 const double R = 1.0 / gsum;
                 // area / (4 pi) R psi(s R)
-                M.add(S.R * R, 0.5 * A2 / kFourPi * span * q.gth[2 * p + 1] * R * fm::exp(-S.c * R));
+                M.add(fma(R, S.scale, -1.0), 0.0, 0.5 * A2 / kFourPi * span * q.gth[2 * p + 1] * R);
             }
         }
     } else {
@@ -281,7 +281,7 @@ __device__ __forceinline__ void gal_moments(Moments<K> &M, const GeoDev &g, cons
                     double d[3];
 #pragma unroll
                     for (int k = 0; k < 3; ++k) d[k] = c[r][0] * E[k] + c[r][1] * A[k] + c[r][2] * B[k];
-                    add_radial<K>(M, S, d, r == 0 ? w : w * e2);
+                    add_radial(M, S, d, r == 0 ? w : w * e2);
                 }
             }
         } else {
@@ -303,37 +303,37 @@ __device__ __forceinline__ void gal_moments(Moments<K> &M, const GeoDev &g, cons
                     double d[3];
 #pragma unroll
                     for (int k = 0; k < 3; ++k) d[k] = (X1[k] + e1 * X2[k]) - e2 * (Y1[k] + e3 * Y2[k]);
-                    add_radial<K>(M, S, d, w);
+                    add_radial(M, S, d, w);
 #pragma unroll
                     for (int k = 0; k < 3; ++k) d[k] = e2 * (X1[k] + e3 * X2[k]) - (Y1[k] + e1 * Y2[k]);
-                    add_radial<K>(M, S, d, w);
+                    add_radial(M, S, d, w);
                 }
             }
         }
     }
 }
 
-// the entry at the frequencies sub, sub + G, ... (KERNEL 1: with the factor 1 + s r)
-template <int KERNEL, int K, int G>
-__device__ __forceinline__ void write_entry(const Moments<K> &M, const NearSeries &S, const FreqDev &f, double rc,
-                                            double num, int sub, int64_t base, int n, double2 *out64, float2 *out32) {
-    const double iR = 1.0 / S.R;
-    for (int l = sub; l < f.L_eval; l += G) {
+// the entry at the frequencies sub, sub + G, ... of band b (RADIAL: no factor e^{-s r_c})
+template <bool RADIAL, int G, int K, bool D>
+__device__ __forceinline__ void write_entry(const Moments<K, D> &M, const NearSeries &S, const FreqDev &f, int b,
+                                            double rc, double num, int sub, int64_t base, int n, double2 *out64,
+                                            float2 *out32) {
+    for (int p = S.first[b] + sub; p < S.first[b + 1]; p += G) {
+        const int l = S.order[p];
         const double sr = f.re[l], si = f.im[l];
-        double2 P, D;
-        M.template eval<KERNEL == 1>((S.c - sr) * iR, -si * iR, P, D);
-        if (KERNEL == 1) {
-            // (1 + s r_c) P + s P' / R
-            const double ar = fma(sr, rc, 1.0), ai = si * rc, br = sr * iR, bi = si * iR;
-            const double pr = ar * P.x - ai * P.y + (br * D.x - bi * D.y);
-            P.y = ar * P.y + ai * P.x + (br * D.y + bi * D.x);
-            P.x = pr;
+        const double2 P = G == 1 ? M.template eval<true>(S.by_freq + (int64_t)p * K, 1, sr, si)
+                                 : M.template eval<false>(S.by_term + p, f.L_eval, sr, si);
+        double vr = P.x, vi = P.y;
+        if (!RADIAL) {
+            // e^{-s r_c}, the products with r_c corrected by what their rounding leaves
+            const double hr = sr * rc, hi = si * rc;
+            const double mag = fm::exp(-hr) * (1.0 - fma(sr, rc, -hr)), lo = fma(si, rc, -hi);
+            double sn, cs;
+            fm::sincos(hi, &sn, &cs);
+            const double er = num * mag * fma(-sn, lo, cs), ei = -num * mag * fma(cs, lo, sn);
+            vr = er * P.x - ei * P.y;
+            vi = er * P.y + ei * P.x;
         }
-        const double mag = num * fm::exp(-sr * rc);
-        double sn, cs;
-        fm::sincos(si * rc, &sn, &cs);
-        const double er = mag * cs, ei = -mag * sn;
-        const double vr = er * P.x - ei * P.y, vi = er * P.y + ei * P.x;
         const int64_t o = base + (int64_t)l * n, om = base + (int64_t)(f.L - 1 - l) * n;
         const bool mir = f.mirror && f.L - 1 - l != l;
         if (out64) {
@@ -346,52 +346,53 @@ __device__ __forceinline__ void write_entry(const Moments<K> &M, const NearSerie
     }
 }
 
-// CLS: Galerkin class (GAL), collocation tier, or the P1 double layer
+// WHAT: Galerkin class (GAL), collocation tier, or the P1 double layer.  blockIdx.y: band
 enum { GAL = 0, COL = 1, P1 = 2 };
 template <int WHAT, int KERNEL, int TIER, int K, int G>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 2)
     near_series_kernel(GeoDev g, QuadDev q, FreqDev f, NearSeries S, const NearPair *__restrict__ pairs,
                        int64_t npairs, const NearBlockDev *__restrict__ blocks, double2 *out64, float2 *out32) {
+    constexpr bool RADIAL = WHAT == GAL && TIER >= GT_EDGE;
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, p = t / G;
     const int sub = (int)(t % G);
     if (p >= npairs) return;   // the G lanes of a pair together
     const NearPair pr = pairs[p];
     const NearBlockDev B = blocks[pr.blk];
-    const int64_t i = B.r0 + pr.i, j = B.c0 + pr.j;
-    double rc, num = 1.0;
-    double z;
-    if constexpr (WHAT == GAL) z = gal_span<TIER>(g, S, i, j, rc);
-    else if constexpr (WHAT == COL) z = near_span(g, S, i, j, rc);
-    else z = p1_span(g, S, i, j, rc);
-    if (!(z <= kNearSeriesMax)) return;
-    Moments<K> M;
+    const int64_t i = B.r0 + pr.i, j = B.c0 + pr.j, base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
+    double rc, half, num = 1.0;
+    if constexpr (WHAT == GAL) gal_span<TIER>(g, i, j, rc, half);
+    else if constexpr (WHAT == COL) near_span(g, i, j, rc, half);
+    else p1_span(g, i, j, rc, half);
+    if (!series_covers(S, rc, half)) return;
+    const double x[3] = {g.xx[i], g.xy[i], g.xz[i]};
+    if (WHAT == COL && KERNEL == 1) num = g.nx[j] * x[0] + g.ny[j] * x[1] + g.nz[j] * x[2] - g.d[j];
+    const int b = blockIdx.y;
+    const Span sp{S.c[b], rc, (RADIAL ? 2.0 : 1.0) / S.half};
+    Moments<K, KERNEL == 1> M;
     M.zero();
     if constexpr (WHAT == GAL) {
-        gal_moments<TIER, K, G>(M, g, q, S, rc, i, j, sub);
+        gal_moments<TIER, G>(M, g, q, sp, i, j, sub);
     } else if constexpr (WHAT == COL) {
-        const double x[3] = {g.xx[i], g.xy[i], g.xz[i]};
-        const double a[3] = {g.ax[j], g.ay[j], g.az[j]}, b[3] = {g.bx[j], g.by[j], g.bz[j]},
+        const double a[3] = {g.ax[j], g.ay[j], g.az[j]}, b3[3] = {g.bx[j], g.by[j], g.bz[j]},
                      c[3] = {g.cx[j], g.cy[j], g.cz[j]};
         if constexpr (TIER == TIER_FAR6) {
             const int64_t T = g.M;
             for (int k = sub; k < 6; k += G) {
                 double ir;
                 const double r = dist3_inv(x[0], x[1], x[2], g.q6x[k * T + j], g.q6y[k * T + j], g.q6z[k * T + j], ir);
-                add_point<KERNEL, K>(M, S, rc, r, ir, g.q6w[k * T + j]);
+                add_point(M, sp, r, ir, g.q6w[k * T + j]);
             }
         } else if constexpr (TIER == TIER_SELF) {
             for (int e = 0; e < 3; ++e) {
-                const double *p1 = e == 0 ? b : (e == 1 ? c : a), *p2 = e == 0 ? c : (e == 1 ? a : b);
+                const double *p1 = e == 0 ? b3 : (e == 1 ? c : a), *p2 = e == 0 ? c : (e == 1 ? a : b3);
                 const double v1[3] = {p1[0], p1[1], p1[2]}, v2[3] = {p2[0], p2[1], p2[2]};
-                add_collapsed<KERNEL, K, G>(M, S, rc, x, x, v1, v2, q.nd, q.gd, 1.0, sub);
+                add_collapsed<G>(M, sp, x, x, v1, v2, q.nd, q.gd, 1.0, sub);
             }
         } else {
-            add_collapsed<KERNEL, K, G>(M, S, rc, x, a, b, c, TIER == TIER_MID4 ? q.n4 : q.n8,
-                                        TIER == TIER_MID4 ? q.g4 : q.g8, 1.0, sub);
+            add_collapsed<G>(M, sp, x, a, b3, c, TIER == TIER_MID4 ? q.n4 : q.n8, TIER == TIER_MID4 ? q.g4 : q.g8,
+                             1.0, sub);
         }
-        if (KERNEL == 1) num = g.nx[j] * x[0] + g.ny[j] * x[1] + g.nz[j] * x[2] - g.d[j];
     } else {
-        const double x[3] = {g.xx[i], g.xy[i], g.xz[i]};
         const int32_t vid = g.dvid[i];
         for (int32_t e = g.pptr[j]; e < g.pptr[j + 1]; ++e) {
             const int64_t tr = g.ptri[e];
@@ -405,32 +406,29 @@ __global__ void __launch_bounds__(256)
                     double ir;
                     const double r =
                         dist3_inv(x[0], x[1], x[2], g.q6x[k * T + tr], g.q6y[k * T + tr], g.q6z[k * T + tr], ir);
-                    add_point<1, K>(M, S, rc, r, ir, nt * g.q6wl[(int64_t)(loc * 6 + k) * T + tr]);
+                    add_point(M, sp, r, ir, nt * g.q6wl[(int64_t)(loc * 6 + k) * T + tr]);
                 }
             } else {
-                const double a[3] = {g.ax[tr], g.ay[tr], g.az[tr]}, b[3] = {g.bx[tr], g.by[tr], g.bz[tr]},
+                const double a[3] = {g.ax[tr], g.ay[tr], g.az[tr]}, b3[3] = {g.bx[tr], g.by[tr], g.bz[tr]},
                              c[3] = {g.cx[tr], g.cy[tr], g.cz[tr]};
-                add_collapsed<1, K, G>(M, S, rc, x, a, b, c, qd >= 2.0 ? q.n4 : q.n8, qd >= 2.0 ? q.g4 : q.g8, nt, sub,
-                                       loc);
+                add_collapsed<G>(M, sp, x, a, b3, c, qd >= 2.0 ? q.n4 : q.n8, qd >= 2.0 ? q.g4 : q.g8, nt, sub, loc);
             }
         }
     }
     M.template finish<G>();
-    if constexpr (WHAT == GAL && TIER >= GT_EDGE)
-        M.template radial<TIER == GT_VERTEX ? 0 : TIER == GT_EDGE ? 1 : 2>(S.c / S.R);
-    const int64_t base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
-    write_entry<KERNEL, K, G>(M, S, f, rc, num, sub, base, B.n, out64, out32);
+    write_entry<RADIAL, G>(M, S, f, b, rc, num, sub, base, B.n, out64, out32);
 }
 
 template <int WHAT, int KERNEL, int TIER, int G>
 void launch(const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S, const NearPair *pairs,
             int64_t npairs, const NearBlockDev *blocks, double2 *o64, float2 *o32, hipStream_t st) {
-    const unsigned nb = (unsigned)((npairs * G + 255) / 256);
+    const dim3 nb((unsigned)((npairs * G + 255) / 256), S.nband);
 #define GACA_SERIES(K) \
     near_series_kernel<WHAT, KERNEL, TIER, K, G><<<nb, 256, 0, st>>>(g, q, f, S, pairs, npairs, blocks, o64, o32)
-    if (S.K == 24) GACA_SERIES(24);
-    else if (S.K == 32) GACA_SERIES(32);
-    else GACA_SERIES(44);
+    if (S.K == 16) GACA_SERIES(16);
+    else if (S.K == 20) GACA_SERIES(20);
+    else if (S.K == 24) GACA_SERIES(24);
+    else GACA_SERIES(30);
 #undef GACA_SERIES
 }
 
@@ -474,10 +472,13 @@ void launch_near_series(int kernel, int tier, const GeoDev &g, const QuadDev &q,
 #undef GACA_NEAR
 }
 
-void launch_near_series_p1(const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
+void launch_near_series_p1(int tier, const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S,
                            const NearPair *pairs, int64_t npairs, const NearBlockDev *blocks, double2 *o64,
                            hipStream_t st) {
-    if (npairs > 0) launch<P1, 1, 0, 8>(g, q, f, S, pairs, npairs, blocks, o64, nullptr, st);
+    if (npairs <= 0) return;
+    // one lane where a pair has six points a triangle (the sums over lanes would cost more than the points)
+    if (tier == 0) launch<P1, 1, 0, 1>(g, q, f, S, pairs, npairs, blocks, o64, nullptr, st);
+    else launch<P1, 1, 0, 4>(g, q, f, S, pairs, npairs, blocks, o64, nullptr, st);
 }
 
 }  // namespace gaca

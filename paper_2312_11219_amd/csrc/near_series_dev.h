@@ -1,4 +1,4 @@
-// Which pairs of the near field the power series in the frequency covers (near_moments.hip): the
+// Which pairs of the near field the Chebyshev series in the distance covers (near_moments.hip): the
 // kernels of both kinds decide by the same functions.
 #pragma once
 
@@ -21,50 +21,49 @@ __device__ __forceinline__ double tri_radius(const GeoDev &g, int64_t t) {
                 dist3(g.cx[t], g.cy[t], g.cz[t], cx, cy, cz));
 }
 
-// Two kernels may round a pair's bound differently: the series takes pairs up to kNearSeriesMax, the
-// kernels that visit the points at every frequency leave out those safely below it.  What both
-// write is the same entry.
-constexpr double kSeriesSafe = kNearSeriesMax * (1.0 - 1e-9);
-
-// Argument of the series' bound; the exponentials at r_c and over the span stay far from the ends
-// of the range of doubles.
-__device__ __forceinline__ double span_bound(const NearSeries &S, double rc, double half) {
-    return fmax(S.R * half, (fabs(S.c) + S.R) * rc * (kNearSeriesMax / 600.0));
+// The series takes these pairs, the kernels that visit the points at every frequency the others.  Two
+// kernels may round a span differently, so the latter (share = 1 - 1e-9) leave out only what is safely
+// covered; what both write is the same entry.
+__device__ __forceinline__ bool series_covers(const NearSeries &S, double rc, double half, double share = 1.0) {
+    return S.K > 0 && half <= S.half * share && rc <= S.rmax * share;
 }
+constexpr double kSeriesSafe = 1.0 - 1e-9;
 
-// the pair's span; returns the argument of the series' bound
+// touching pairs: the distances reach from 0 to half
 template <int TIER>
-__device__ __forceinline__ double gal_span(const GeoDev &g, const NearSeries &S, int64_t i, int64_t j, double &rc) {
+__device__ __forceinline__ void gal_span(const GeoDev &g, int64_t i, int64_t j, double &rc, double &half) {
     if (TIER == GT_EDGE || TIER == GT_VERTEX || TIER == GT_COINC) {
         rc = 0.0;
-        return fmax(fabs(S.c), S.R) * (TIER == GT_COINC ? g.h[i] : g.h[i] + g.h[j]);
+        half = TIER == GT_COINC ? g.h[i] : g.h[i] + g.h[j];
+    } else {
+        span_of(dist3(g.xx[i], g.xy[i], g.xz[i], g.xx[j], g.xy[j], g.xz[j]), tri_radius(g, i) + tri_radius(g, j), rc,
+                half);
     }
-    double half;
-    span_of(dist3(g.xx[i], g.xy[i], g.xz[i], g.xx[j], g.xy[j], g.xz[j]), tri_radius(g, i) + tri_radius(g, j), rc, half);
-    return span_bound(S, rc, half);
 }
 
-__device__ __forceinline__ double near_span(const GeoDev &g, const NearSeries &S, int64_t i, int64_t j, double &rc) {
-    double half;
+__device__ __forceinline__ void near_span(const GeoDev &g, int64_t i, int64_t j, double &rc, double &half) {
     span_of(i == j ? 0.0 : dist3(g.xx[i], g.xy[i], g.xz[i], g.xx[j], g.xy[j], g.xz[j]), tri_radius(g, j), rc, half);
-    return span_bound(S, rc, half);
 }
 
 // The distances to a patch reach up to that of its farthest vertex, and down to the vertex j's less
 // the patch's longest edge at it.
-__device__ __forceinline__ double p1_span(const GeoDev &g, const NearSeries &S, int64_t i, int64_t j, double &rc) {
-    const double x = g.xx[i], y = g.xy[i], z = g.xz[i], vx = g.xx[j], vy = g.xy[j], vz = g.xz[j];
-    double rad = 0.0, top = 0.0;
+__device__ __forceinline__ void p1_span(const GeoDev &g, int64_t i, int64_t j, double &rc, double &half) {
+    const double x[3] = {g.xx[i], g.xy[i], g.xz[i]}, v[3] = {g.xx[j], g.xy[j], g.xz[j]};
+    double rad2 = 0.0, top2 = 0.0;
+    auto sq = [](const double *o, double px, double py, double pz) {
+        return (px - o[0]) * (px - o[0]) + (py - o[1]) * (py - o[1]) + (pz - o[2]) * (pz - o[2]);
+    };
     for (int32_t e = g.pptr[j]; e < g.pptr[j + 1]; ++e) {
         const int64_t t = g.ptri[e];
-        rad = fmax(rad, fmax(fmax(dist3(vx, vy, vz, g.ax[t], g.ay[t], g.az[t]), dist3(vx, vy, vz, g.bx[t], g.by[t], g.bz[t])),
-                             dist3(vx, vy, vz, g.cx[t], g.cy[t], g.cz[t])));
-        top = fmax(top, fmax(fmax(dist3(x, y, z, g.ax[t], g.ay[t], g.az[t]), dist3(x, y, z, g.bx[t], g.by[t], g.bz[t])),
-                             dist3(x, y, z, g.cx[t], g.cy[t], g.cz[t])));
+        rad2 = fmax(rad2, fmax(fmax(sq(v, g.ax[t], g.ay[t], g.az[t]), sq(v, g.bx[t], g.by[t], g.bz[t])),
+                               sq(v, g.cx[t], g.cy[t], g.cz[t])));
+        top2 = fmax(top2, fmax(fmax(sq(x, g.ax[t], g.ay[t], g.az[t]), sq(x, g.bx[t], g.by[t], g.bz[t])),
+                               sq(x, g.cx[t], g.cy[t], g.cz[t])));
     }
-    const double lo = fmax(dist3(x, y, z, vx, vy, vz) - rad, 0.0);
+    const double rad = sqrt(rad2), top = sqrt(top2);
+    const double lo = fmax(dist3(x[0], x[1], x[2], v[0], v[1], v[2]) - rad, 0.0);
     rc = 0.5 * (lo + top);
-    return span_bound(S, rc, 0.5 * (top - lo));
+    half = 0.5 * (top - lo);
 }
 
 }  // namespace gaca
