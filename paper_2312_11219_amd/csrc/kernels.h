@@ -61,19 +61,33 @@ void launch_eval_gp1(int op, const GeoDev &g, const QuadDev &q, const FreqDev &f
                      const int32_t *far, double2 *out, hipStream_t st);
 
 // The same near field by triangle pairs (csrc/near_gp1.hip): pairs (ti, tj) sorted by ti, then tj
-// (row ti: rowptr[ti] .. rowptr[ti + 1]), and the indices of the pairs of each class.
+// (row ti: rowptr[ti] .. rowptr[ti + 1]), in chunks of whole rows whose integrals fit the buffer, and
+// in `list` the indices of the pairs of each chunk's classes.
 enum Gp1Class : int32_t { GP1_FAR = 0, GP1_MID = 1, GP1_NEAR = 2, GP1_VERTEX = 3 /* 3, 4, 5: 1, 2, 3 shared vertices */ };
 constexpr int kGp1Classes = 6;
+struct Gp1Chunk {
+    int32_t t0, t1;                   // rows
+    int64_t p0;                       // first pair
+    int64_t first[kGp1Classes + 1];   // class c: list[first[c] .. first[c + 1])
+};
 struct Gp1Pairs {
-    int64_t np;
     const int2 *pairs;
     const int64_t *rowptr;
     const int32_t *list;
-    int64_t first[kGp1Classes + 1];   // class c: list[first[c] .. first[c + 1])
+    const Gp1Chunk *chunks;           // host
+    int nchunk;
 };
 constexpr int64_t kGp1Slot = 10 * 16;   // bytes per pair and frequency of the pair buffer
-void launch_gp1_classes(const GeoDev &g, const int2 *pairs, int64_t np, uint8_t *cls, hipStream_t st);
-// buf: np * nfc slots; the frequencies go in chunks of nfc
+// The pairs of the rows from bitmaps: row ti has a bit for every tj in one of the sets rowset[rowsetptr[ti]]
+// .. of `words` 64-bit words; their classes, counted per chunk (chunk_of: first rows of the nchunk chunks,
+// count[nchunk][kGp1Classes] zeroed by the call)
+void launch_gp1_fill(const GeoDev &g, const uint64_t *sets, int words, const int32_t *rowsetptr,
+                     const int32_t *rowset, const int64_t *rowptr, int64_t T, const int32_t *chunk_of, int nchunk,
+                     int2 *pairs, uint8_t *cls, unsigned long long *count, hipStream_t st);
+// list of every chunk's classes; next[nchunk][kGp1Classes]: their first places, moved on by the call
+void launch_gp1_list(const int2 *pairs, const uint8_t *cls, int64_t np, const int32_t *chunk_of, int nchunk,
+                     unsigned long long *next, int32_t *list, hipStream_t st);
+// buf: (pairs of the largest chunk) * nfc slots; the frequencies go in chunks of nfc
 void launch_near_gp1_pairs(int op, const GeoDev &g, const QuadDev &q, const FreqDev &f, const Gp1Pairs &P,
                            double2 *buf, int nfc, const NearPair *vp, int64_t nvp,
                            const NearBlockDev *blocks, double2 *out64, hipStream_t st);

@@ -422,11 +422,13 @@ struct gaca_problem {
     double p1_near_points = 0.0;         // quadrature points of the near field per frequency
     int64_t p1_far_pairs = 0;            // near pairs with the 6-point rule on every triangle (the first ones)
     DevBuf d_p1i;
-    // Galerkin P1: the triangle pairs of the near field and the buffer of their integrals (kept
-    // for the problem's builds; nfc frequencies at a time, 0: no pair list, entry by entry)
+    // Galerkin P1: the triangle pairs of the near field and the buffer of their integrals (up to
+    // kGp1Buffer, kept for the problem's builds; nfc frequencies at a time, 0: no pair list, entry by entry)
     DevBuf d_gp1_pairs, d_gp1_rowptr, d_gp1_list, d_gp1_buf;
     Gp1Pairs gp1{};
+    std::vector<Gp1Chunk> gp1_chunks;
     int gp1_nfc = 0;
+    size_t gp1_bytes = 0;
     ClusterTree tree;
     Partition part;
     int32_t L = 0;
@@ -978,93 +980,125 @@ static void upload_problem_p1(gaca_problem *p) {
     set_leaves(p);
 }
 
-// Triangle pairs of the Galerkin P1 near field: every (ti, tj) with a near vertex pair on it,
-// grouped by the class that the device finds (the rules' comparisons stay in one place).  Under
-// a memory cap, or where the memory does not suffice, there is no list and the near field is
-// evaluated entry by entry.
+// Triangle pairs of the Galerkin P1 near field: every (ti, tj) with a near vertex pair on it.  The
+// host marks the triangles that a row cluster's blocks reach in one bitmap per cluster and counts the
+// pairs; the device lists them and groups them by class.  Under a memory cap, or where the memory does
+// not suffice, there is no list and the near field is evaluated entry by entry.
+constexpr int64_t kGp1Buffer = (int64_t)512 << 20;
 static void upload_gp1_pairs(gaca_problem *p) {
     gaca_context *ctx = p->ctx;
     if (ctx->limit) return;
     const int64_t T = p->mesh.M;
-    // column clusters met by each row cluster, and the triangles of a cluster's patches
-    std::map<std::pair<int64_t, int64_t>, std::vector<std::pair<int64_t, int64_t>>> cols_of;
-    std::map<std::pair<int64_t, int64_t>, std::vector<int32_t>> tris_of;
+    // a pair of triangles lies on at most nine vertex pairs, of which the points count 36 each
+    if (T > INT32_MAX || p->p1_near_points / (36.0 * 9.0) > (double)INT32_MAX) return;
+    const int words = (int)((T + 63) / 64);
+    std::map<std::pair<int64_t, int64_t>, int32_t> set_of;   // row cluster -> bitmap
+    for (const auto &nb : p->part.near) set_of.emplace(std::make_pair(nb[0], nb[1]), (int32_t)set_of.size());
+    if ((double)set_of.size() * words * 8.0 > 1073741824.0) return;
+    std::vector<uint64_t> sets(set_of.size() * words, 0);
     for (const auto &nb : p->part.near) {
-        cols_of[{nb[0], nb[1]}].push_back({nb[2], nb[3]});
-        for (int s = 0; s < 4; s += 2) {
-            auto &t = tris_of[{nb[s], nb[s + 1]}];
-            if (!t.empty()) continue;
-            t.assign(p->ptri.begin() + p->pptr[nb[s]], p->ptri.begin() + p->pptr[nb[s] + nb[s + 1]]);
-            std::sort(t.begin(), t.end());
-            t.erase(std::unique(t.begin(), t.end()), t.end());
-        }
+        uint64_t *s = &sets[(size_t)set_of[{nb[0], nb[1]}] * words];
+        for (int32_t e = p->pptr[nb[2]]; e < p->pptr[nb[2] + nb[3]]; ++e) s[p->ptri[e] >> 6] |= 1ull << (p->ptri[e] & 63);
     }
-    std::vector<std::vector<const std::vector<int32_t> *>> sets(T);
-    for (const auto &rc : cols_of)
-        for (int32_t ti : tris_of[rc.first])
-            for (const auto &c : rc.second) sets[ti].push_back(&tris_of[c]);
+    // the bitmaps of each row: those of the clusters with a vertex of the triangle
+    std::vector<int32_t> rowsetptr(T + 1, 0), rowset, last(T, -1);
+    std::vector<std::pair<int32_t, int32_t>> on;
+    for (const auto &rc : set_of)
+        for (int32_t e = p->pptr[rc.first.first]; e < p->pptr[rc.first.first + rc.first.second]; ++e)
+            if (last[p->ptri[e]] != rc.second) {
+                last[p->ptri[e]] = rc.second;
+                on.push_back({p->ptri[e], rc.second});
+                ++rowsetptr[p->ptri[e] + 1];
+            }
+    for (int64_t t = 0; t < T; ++t) rowsetptr[t + 1] += rowsetptr[t];
+    rowset.resize(on.size());
+    {
+        std::vector<int32_t> at(rowsetptr.begin(), rowsetptr.end() - 1);
+        for (const auto &o : on) rowset[at[o.first]++] = o.second;
+    }
     std::vector<int64_t> rowptr(T + 1, 0);
-    std::vector<int2> pairs;
-    std::vector<int32_t> mark(T, -1), row;
-    row.reserve(T);
-    for (int64_t ti = 0; ti < T; ++ti) {
-        row.clear();
-        for (const auto *set : sets[ti])
-            for (int32_t tj : *set)
-                if (mark[tj] != ti) {
-                    mark[tj] = (int32_t)ti;
-                    row.push_back(tj);
-                }
-        if ((int64_t)row.size() * 8 > T) {   // a full row: in order by its marks
-            for (int32_t tj = 0; tj < T; ++tj)
-                if (mark[tj] == ti) pairs.push_back(make_int2((int)ti, tj));
-        } else {
-            std::sort(row.begin(), row.end());
-            for (int32_t tj : row) pairs.push_back(make_int2((int)ti, tj));
-        }
-        rowptr[ti + 1] = (int64_t)pairs.size();
+    std::vector<uint64_t> row(words);
+    for (int64_t t = 0; t < T; ++t) {
+        std::fill(row.begin(), row.end(), 0);
+        for (int32_t s = rowsetptr[t]; s < rowsetptr[t + 1]; ++s)
+            for (int w = 0; w < words; ++w) row[w] |= sets[(size_t)rowset[s] * words + w];
+        int64_t n = 0;
+        for (int w = 0; w < words; ++w) n += __builtin_popcountll(row[w]);
+        rowptr[t + 1] = rowptr[t] + n;
     }
-    const int64_t np = (int64_t)pairs.size();
+    const int64_t np = rowptr[T];
     if (np == 0 || np > INT32_MAX) return;
+    // as many frequencies as the buffer holds of all pairs; else two (the kernels take two per point),
+    // and the rows in chunks
+    size_t fb = 0, tb = 0;
+    if (hipMemGetInfo(&fb, &tb) != hipSuccess) {
+        (void)hipGetLastError();
+        fb = 0;
+    }
+    const int64_t budget = std::min<int64_t>(kGp1Buffer, (int64_t)(fb / 8)) / kGp1Slot;   // pairs times frequencies
+    const int nfc = (int)std::max<int64_t>(std::min(2, p->f.L_eval), std::min<int64_t>(p->f.L_eval, budget / np));
+    std::vector<Gp1Chunk> chunks;
+    std::vector<int32_t> chunk_of;
+    int64_t most = 0;
+    for (int64_t t = 0; t < T;) {
+        int64_t e = t + 1;
+        while (e < T && rowptr[e + 1] - rowptr[t] <= budget / nfc) ++e;
+        Gp1Chunk c{};
+        c.t0 = (int32_t)t;
+        c.t1 = (int32_t)e;
+        c.p0 = rowptr[t];
+        most = std::max(most, rowptr[e] - rowptr[t]);
+        chunks.push_back(c);
+        chunk_of.push_back(c.t0);
+        t = e;
+    }
+    const int nch = (int)chunks.size();
+    // lists and buffer within an eighth of the free memory
+    if ((double)most * nfc * kGp1Slot + 13.0 * np > 0.125 * (double)fb) return;
     try {
-        DevBuf cls;
-        p->d_gp1_pairs.upload(ctx, pairs);
-        p->d_gp1_rowptr.upload(ctx, rowptr);
+        DevBuf dsets, dptr, dset, dchunk, dcnt, cls;
+        dsets.upload(ctx, sets);
+        dptr.upload(ctx, rowsetptr);
+        dset.upload(ctx, rowset);
+        dchunk.upload(ctx, chunk_of);
+        dcnt.alloc(ctx, (size_t)nch * kGp1Classes * sizeof(unsigned long long));
         cls.alloc(ctx, np);
-        launch_gp1_classes(p->g, p->d_gp1_pairs.as<int2>(), np, cls.as<uint8_t>(), ctx->stream);
+        p->d_gp1_rowptr.upload(ctx, rowptr);
+        p->d_gp1_pairs.alloc(ctx, (size_t)np * sizeof(int2));
+        p->d_gp1_list.alloc(ctx, (size_t)np * sizeof(int32_t));
+        launch_gp1_fill(p->g, dsets.as<uint64_t>(), words, dptr.as<int32_t>(), dset.as<int32_t>(),
+                        p->d_gp1_rowptr.as<int64_t>(), T, dchunk.as<int32_t>(), nch, p->d_gp1_pairs.as<int2>(),
+                        cls.as<uint8_t>(), dcnt.as<unsigned long long>(), ctx->stream);
         GACA_HIP_CHECK(hipGetLastError());
         GACA_HIP_CHECK(hipStreamSynchronize(ctx->stream));
-        std::vector<uint8_t> hc(np);
-        GACA_HIP_CHECK(hipMemcpy(hc.data(), cls.ptr, np, hipMemcpyDeviceToHost));
-        int64_t *first = p->gp1.first;
-        std::fill(first, first + kGp1Classes + 1, (int64_t)0);
-        for (uint8_t c : hc) ++first[c + 1];
-        for (int c = 0; c < kGp1Classes; ++c) first[c + 1] += first[c];
-        std::vector<int32_t> list(np);
-        std::vector<int64_t> at(first, first + kGp1Classes);
-        for (int64_t t = 0; t < np; ++t) list[at[hc[t]]++] = (int32_t)t;
-        p->d_gp1_list.upload(ctx, list);
-        // as many frequencies as 2 GiB or an eighth of the free memory hold
-        size_t fb = 0, tb = 0;
-        if (hipMemGetInfo(&fb, &tb) != hipSuccess) {
-            (void)hipGetLastError();
-            fb = 0;
-        }
-        const int64_t budget = std::min<int64_t>((int64_t)2 << 30, (int64_t)(fb / 8));
-        p->gp1_nfc = (int)std::min<int64_t>(p->f.L_eval, budget / (np * kGp1Slot));
-    } catch (const Error &) {   // the entry-by-entry kernel needs none of this
-        p->gp1_nfc = 0;
-    }
-    if (p->gp1_nfc == 0) {
+        std::vector<unsigned long long> cnt((size_t)nch * kGp1Classes);
+        GACA_HIP_CHECK(hipMemcpy(cnt.data(), dcnt.ptr, cnt.size() * sizeof(cnt[0]), hipMemcpyDeviceToHost));
+        int64_t at = 0;
+        for (int c = 0; c < nch; ++c)
+            for (int k = 0; k < kGp1Classes; ++k) {
+                chunks[c].first[k] = at;
+                const int64_t n = (int64_t)cnt[c * kGp1Classes + k];
+                cnt[c * kGp1Classes + k] = (unsigned long long)at;
+                at += n;
+                chunks[c].first[k + 1] = at;
+            }
+        GACA_HIP_CHECK(hipMemcpy(dcnt.ptr, cnt.data(), cnt.size() * sizeof(cnt[0]), hipMemcpyHostToDevice));
+        launch_gp1_list(p->d_gp1_pairs.as<int2>(), cls.as<uint8_t>(), np, dchunk.as<int32_t>(), nch,
+                        dcnt.as<unsigned long long>(), p->d_gp1_list.as<int32_t>(), ctx->stream);
+        GACA_HIP_CHECK(hipGetLastError());
+        GACA_HIP_CHECK(hipStreamSynchronize(ctx->stream));
+    } catch (const Error &e) {   // the entry-by-entry kernel needs none of this
+        if (e.code != GACA_ERR_OOM) throw;
         p->d_gp1_pairs.release();
         p->d_gp1_rowptr.release();
         p->d_gp1_list.release();
         return;
     }
-    p->gp1.np = np;
-    p->gp1.pairs = p->d_gp1_pairs.as<int2>();
-    p->gp1.rowptr = p->d_gp1_rowptr.as<int64_t>();
-    p->gp1.list = p->d_gp1_list.as<int32_t>();
+    p->gp1_nfc = nfc;
+    p->gp1_bytes = (size_t)most * nfc * kGp1Slot;
+    p->gp1_chunks.swap(chunks);
+    p->gp1 = Gp1Pairs{p->d_gp1_pairs.as<int2>(), p->d_gp1_rowptr.as<int64_t>(), p->d_gp1_list.as<int32_t>(),
+                      p->gp1_chunks.data(), nch};
 }
 
 static void upload_freq(gaca_problem *p) {
@@ -2414,14 +2448,16 @@ static bool build_ops(gaca_problem *p, const std::vector<gaca_kernel> &kernels,
             }
             if (p->scheme == GACA_GALERKIN_P1) {
                 const int op = kernels[w] == GACA_HYP ? 0 : 1;
-                if (p->gp1_nfc > 0 && !p->d_gp1_buf.ptr) {
+                // a cap that another problem has brought to the context since leaves the memory to the rest
+                bool by_pairs = p->gp1_nfc > 0 && (!ctx->limit || p->d_gp1_buf.ptr);
+                if (by_pairs && !p->d_gp1_buf.ptr) {
                     try {
-                        p->d_gp1_buf.alloc(ctx, (size_t)p->gp1.np * p->gp1_nfc * kGp1Slot);
+                        p->d_gp1_buf.alloc(ctx, p->gp1_bytes);
                     } catch (const Error &) {
-                        p->gp1_nfc = 0;
+                        by_pairs = false;
                     }
                 }
-                if (p->gp1_nfc > 0)
+                if (by_pairs)
                     launch_near_gp1_pairs(op, p->g, p->q, p->f, p->gp1, p->d_gp1_buf.as<double2>(), p->gp1_nfc,
                                           p->d_pairs[0].as<NearPair>(), p->npairs[0],
                                           p->d_nblocks.as<NearBlockDev>(), n64, st);

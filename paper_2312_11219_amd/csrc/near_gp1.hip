@@ -14,7 +14,8 @@
 //                      points once per pair, through LDS
 //   touching           one wave per pair over the n^4 points, all regions per point
 // Every lane takes NF frequencies per point (the distance and the weights are shared).  Sums over
-// lanes are in a fixed order.  The pair buffer holds a chunk of frequencies at a time.
+// lanes are in a fixed order.  The pair buffer (up to 512 MiB) holds a chunk of frequencies at a time, and
+// on larger meshes a chunk of the rows ti, whose part of every entry is added in turn.
 #include <hip/hip_runtime.h>
 
 #include "device_util.h"
@@ -164,29 +165,104 @@ struct PairArgs {
     const int32_t *list;     // the pairs of the class
     int64_t cnt;
     int l0, nfc;             // chunk of frequencies [l0, l0 + nfc)
-    double2 *buf;            // [pair][nfc][10]
+    int64_t p0;              // first pair of the buffer
+    double2 *buf;            // [pair - p0][nfc][10]
 };
 
 }  // namespace
 
-__global__ void __launch_bounds__(256) gp1_class_kernel(GeoDev g, const int2 *pairs, int64_t np, uint8_t *cls) {
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (p >= np) return;
-    const int ti = pairs[p].x, tj = pairs[p].y;
+__device__ __forceinline__ int gp1_class(const GeoDev &g, int ti, int tj) {
     const int32_t vi[3] = {g.tv0[ti], g.tv1[ti], g.tv2[ti]}, vj[3] = {g.tv0[tj], g.tv1[tj], g.tv2[tj]};
     int shared = 0;
     for (int x = 0; x < 3; ++x)
         for (int y = 0; y < 3; ++y) shared += vi[x] == vj[y];
-    if (shared > 0) {
-        cls[p] = (uint8_t)(GP1_VERTEX + shared - 1);
-        return;
-    }
+    if (shared > 0) return GP1_VERTEX + shared - 1;
     GP1Tri Ti, Tj;
     gp1_load(g, ti, Ti);
     gp1_load(g, tj, Tj);
     const double dcx = Ti.c[0] - Tj.c[0], dcy = Ti.c[1] - Tj.c[1], dcz = Ti.c[2] - Tj.c[2];
     const double qd = sqrt(dcx * dcx + dcy * dcy + dcz * dcz) / fmax(Ti.h, Tj.h);
-    cls[p] = qd >= 4.0 ? GP1_FAR : qd >= 2.0 ? GP1_MID : GP1_NEAR;
+    return qd >= 4.0 ? GP1_FAR : qd >= 2.0 ? GP1_MID : GP1_NEAR;
+}
+
+// the chunk of row ti: the last with chunk_of[c] <= ti
+__device__ __forceinline__ int gp1_chunk(const int32_t *chunk_of, int nchunk, int ti) {
+    int lo = 0, hi = nchunk - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (chunk_of[mid] <= ti) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+__global__ void __launch_bounds__(256) gp1_zero_kernel(unsigned long long *v, int n) {
+    for (int i = threadIdx.x; i < n; i += 256) v[i] = 0;
+}
+
+// one wave per row: a lane ORs a word of the row's sets and writes its bits after those of the lanes below
+__global__ void __launch_bounds__(256)
+    gp1_fill_kernel(GeoDev g, const uint64_t *sets, int words, const int32_t *rowsetptr, const int32_t *rowset,
+                    const int64_t *rowptr, int64_t T, const int32_t *chunk_of, int nchunk, int2 *pairs, uint8_t *cls,
+                    unsigned long long *count) {
+    const int64_t ti = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (ti >= T) return;   // the whole wave; no barrier below
+    int64_t at = rowptr[ti];
+    int n[kGp1Classes] = {0, 0, 0, 0, 0, 0};
+    for (int w0 = 0; w0 < words; w0 += 64) {
+        const int w = w0 + lane;
+        uint64_t bits = 0;
+        if (w < words)
+            for (int s = rowsetptr[ti]; s < rowsetptr[ti + 1]; ++s) bits |= sets[(int64_t)rowset[s] * words + w];
+        int before = __popcll(bits);   // inclusive prefix sum
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(before, d, 64);
+            if (lane >= d) before += v;
+        }
+        int64_t p = at + before - __popcll(bits);
+        at += __shfl(before, 63, 64);
+        while (bits) {
+            const int tj = 64 * w + __ffsll((unsigned long long)bits) - 1;
+            bits &= bits - 1;
+            const int c = gp1_class(g, (int)ti, tj);
+            pairs[p] = make_int2((int)ti, tj);
+            cls[p++] = (uint8_t)c;
+#pragma unroll
+            for (int k = 0; k < kGp1Classes; ++k) n[k] += c == k;
+        }
+    }
+    const int ch = gp1_chunk(chunk_of, nchunk, (int)ti);
+#pragma unroll
+    for (int k = 0; k < kGp1Classes; ++k) {
+        int s = n[k];
+        for (int d = 32; d > 0; d >>= 1) s += __shfl_down(s, d, 64);
+        if (lane == 0 && s > 0) atomicAdd(&count[ch * kGp1Classes + k], (unsigned long long)s);
+    }
+}
+
+// The order within a class is that of the waves' arrival: a pair's integrals have their own place.
+__global__ void __launch_bounds__(256)
+    gp1_list_kernel(const int2 *pairs, const uint8_t *cls, int64_t np, const int32_t *chunk_of, int nchunk,
+                    unsigned long long *next, int32_t *list) {
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    int key = -1;
+    if (p < np) key = gp1_chunk(chunk_of, nchunk, pairs[p].x) * kGp1Classes + cls[p];
+    // one place for all lanes of the wave with the same key
+    unsigned long long left = __ballot(key >= 0);
+    while (left) {
+        const int k = __builtin_amdgcn_readlane(key, __ffsll(left) - 1);
+        const unsigned long long same = __ballot(key == k);
+        left &= ~same;
+        if (key == k) {
+            const int leader = __ffsll(same) - 1;
+            unsigned long long base = 0;
+            if (lane == leader) base = atomicAdd(&next[k], (unsigned long long)__popcll(same));
+            base = __shfl(base, leader, 64);
+            list[base + __popcll(same & ((1ull << lane) - 1))] = (int32_t)p;
+        }
+    }
 }
 
 // 6 x 6 points, one lane per pair; collapsed n4 x n4 on both, 16 lanes per pair
@@ -241,7 +317,7 @@ __global__ void __launch_bounds__(256) gp1_product_kernel(PairArgs A) {
         }
     }
     const int id[3] = {0, 1, 2};
-    store_local<LG>(M, on && sub == 0, nl, id, id, A.buf + ((int64_t)p * A.nfc + k0) * 10);
+    store_local<LG>(M, on && sub == 0, nl, id, id, A.buf + ((p - A.p0) * A.nfc + k0) * 10);
 }
 
 // disjoint pairs with q < 2: outer collapsed n x n on ti, inner rule split at the closest point
@@ -302,7 +378,7 @@ __global__ void __launch_bounds__(64) gp1_near_kernel(PairArgs A) {
             }
         }
     const int id[3] = {0, 1, 2};
-    store_local<6>(M, lane == 0, nl, id, id, A.buf + ((int64_t)p * A.nfc + k0) * 10);
+    store_local<6>(M, lane == 0, nl, id, id, A.buf + ((p - A.p0) * A.nfc + k0) * 10);
 }
 
 // touching pairs (REL shared vertices) by the regularising maps
@@ -381,16 +457,17 @@ __global__ void __launch_bounds__(64) gp1_touch_kernel(PairArgs A) {
                 add_point<OP>(x, lx, y, ly, w0 * jac, Ti.n, A.f, l0, nl, M);
             }
         }
-    store_local<6>(M, lane == 0, nl, pa, pb, A.buf + ((int64_t)p * A.nfc + k0) * 10);
+    store_local<6>(M, lane == 0, nl, pa, pb, A.buf + ((p - A.p0) * A.nfc + k0) * 10);
 }
 
-// Entries of the chunk's frequencies from the pair integrals: one thread per (vertex pair, frequency)
+// The part of the rows [t0, t1) in the entries of the chunk's frequencies, from the pair integrals: one
+// thread per (vertex pair, frequency).  The first chunk of rows (t0 = 0) sets the entries, others add.
 template <int OP>
 __global__ void __launch_bounds__(256)
     gp1_assemble_kernel(GeoDev g, FreqDev f, const NearPair *__restrict__ vp, int64_t nvp,
                         const NearBlockDev *__restrict__ blocks, const int64_t *__restrict__ rowptr,
-                        const int2 *__restrict__ pairs, const double2 *__restrict__ buf, int l0, int nfc,
-                        double2 *out64) {
+                        const int2 *__restrict__ pairs, const double2 *__restrict__ buf, int l0, int nfc, int t0,
+                        int t1, int64_t p0, double2 *out64) {
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (p >= nvp) return;
     const int k = blockIdx.y, l = l0 + k;
@@ -400,8 +477,11 @@ __global__ void __launch_bounds__(256)
     const double sr = f.re[l], si = f.im[l];
     const double s2r = sr * sr - si * si, s2i = 2.0 * sr * si;
     double ar = 0.0, ai = 0.0;
+    bool any = false;
     for (int32_t e = g.pptr[i]; e < g.pptr[i + 1]; ++e) {
         const int ti = g.ptri[e], a = g.ploc[e];
+        if (ti < t0 || ti >= t1) continue;
+        any = true;
         const int64_t q0 = rowptr[ti], q1 = rowptr[ti + 1];
         double ca[3];
         if (OP == 0) gp1_curl(g, ti, a, ca);
@@ -413,7 +493,7 @@ __global__ void __launch_bounds__(256)
                 if (pairs[mid].y < tj) lo = mid + 1;
                 else hi = mid;
             }
-            const double2 *slot = buf + (lo * nfc + k) * 10;
+            const double2 *slot = buf + ((lo - p0) * nfc + k) * 10;
             const double2 M = slot[3 * a + b];
             if (OP == 1) {
                 ar += M.x;
@@ -430,20 +510,35 @@ __global__ void __launch_bounds__(256)
         }
     }
     const int64_t base = B.off + (int64_t)pr.i * f.L * B.n + pr.j;
+    if (t0 > 0) {
+        if (!any) return;
+        const double2 s = out64[base + (int64_t)l * B.n];
+        ar += s.x;
+        ai += s.y;
+    }
     out64[base + (int64_t)l * B.n] = make_double2(ar, ai);
     if (f.mirror && f.L - 1 - l != l) out64[base + (int64_t)(f.L - 1 - l) * B.n] = make_double2(ar, -ai);
 }
 
-void launch_gp1_classes(const GeoDev &g, const int2 *pairs, int64_t np, uint8_t *cls, hipStream_t st) {
-    if (np > 0) gp1_class_kernel<<<(unsigned)((np + 255) / 256), 256, 0, st>>>(g, pairs, np, cls);
+void launch_gp1_fill(const GeoDev &g, const uint64_t *sets, int words, const int32_t *rowsetptr,
+                     const int32_t *rowset, const int64_t *rowptr, int64_t T, const int32_t *chunk_of, int nchunk,
+                     int2 *pairs, uint8_t *cls, unsigned long long *count, hipStream_t st) {
+    gp1_zero_kernel<<<1, 256, 0, st>>>(count, nchunk * kGp1Classes);
+    gp1_fill_kernel<<<(unsigned)((T + 3) / 4), 256, 0, st>>>(g, sets, words, rowsetptr, rowset, rowptr, T, chunk_of,
+                                                            nchunk, pairs, cls, count);
+}
+
+void launch_gp1_list(const int2 *pairs, const uint8_t *cls, int64_t np, const int32_t *chunk_of, int nchunk,
+                     unsigned long long *next, int32_t *list, hipStream_t st) {
+    gp1_list_kernel<<<(unsigned)((np + 255) / 256), 256, 0, st>>>(pairs, cls, np, chunk_of, nchunk, next, list);
 }
 
 template <int OP>
-static void launch_pairs(const Gp1Pairs &P, PairArgs A, hipStream_t st) {
+static void launch_pairs(const Gp1Pairs &P, const Gp1Chunk &C, PairArgs A, hipStream_t st) {
     const unsigned ny = (unsigned)((A.nfc + NF - 1) / NF);
     auto cls = [&](int c) {
-        A.list = P.list + P.first[c];
-        A.cnt = P.first[c + 1] - P.first[c];
+        A.list = P.list + C.first[c];
+        A.cnt = C.first[c + 1] - C.first[c];
         return A.cnt > 0;
     };
     // the classes with the most points per pair first
@@ -455,21 +550,28 @@ static void launch_pairs(const Gp1Pairs &P, PairArgs A, hipStream_t st) {
     if (cls(GP1_FAR)) gp1_product_kernel<OP, false><<<dim3((unsigned)((A.cnt + 255) / 256), ny), 256, 0, st>>>(A);
 }
 
+template <int OP>
+static void near_gp1_pairs(const GeoDev &g, const QuadDev &q, const FreqDev &f, const Gp1Pairs &P, double2 *buf,
+                           int nfc_max, const NearPair *vp, int64_t nvp, const NearBlockDev *blocks,
+                           double2 *out64, hipStream_t st) {
+    for (int l0 = 0; l0 < f.L_eval; l0 += nfc_max) {
+        const int nfc = f.L_eval - l0 < nfc_max ? f.L_eval - l0 : nfc_max;
+        const dim3 grid((unsigned)((nvp + 255) / 256), (unsigned)nfc);
+        for (int c = 0; c < P.nchunk; ++c) {
+            const Gp1Chunk &C = P.chunks[c];
+            launch_pairs<OP>(P, C, PairArgs{g, q, f, P.pairs, nullptr, 0, l0, nfc, C.p0, buf}, st);
+            gp1_assemble_kernel<OP><<<grid, 256, 0, st>>>(g, f, vp, nvp, blocks, P.rowptr, P.pairs, buf, l0, nfc, C.t0,
+                                                          C.t1, C.p0, out64);
+        }
+    }
+}
+
 void launch_near_gp1_pairs(int op, const GeoDev &g, const QuadDev &q, const FreqDev &f, const Gp1Pairs &P,
                            double2 *buf, int nfc_max, const NearPair *vp, int64_t nvp,
                            const NearBlockDev *blocks, double2 *out64, hipStream_t st) {
     if (nvp <= 0) return;
-    for (int l0 = 0; l0 < f.L_eval; l0 += nfc_max) {
-        const int nfc = f.L_eval - l0 < nfc_max ? f.L_eval - l0 : nfc_max;
-        PairArgs A{g, q, f, P.pairs, nullptr, 0, l0, nfc, buf};
-        if (op == 0) launch_pairs<0>(P, A, st);
-        else launch_pairs<1>(P, A, st);
-        const dim3 grid((unsigned)((nvp + 255) / 256), (unsigned)nfc);
-        if (op == 0)
-            gp1_assemble_kernel<0><<<grid, 256, 0, st>>>(g, f, vp, nvp, blocks, P.rowptr, P.pairs, buf, l0, nfc, out64);
-        else
-            gp1_assemble_kernel<1><<<grid, 256, 0, st>>>(g, f, vp, nvp, blocks, P.rowptr, P.pairs, buf, l0, nfc, out64);
-    }
+    if (op == 0) near_gp1_pairs<0>(g, q, f, P, buf, nfc_max, vp, nvp, blocks, out64, st);
+    else near_gp1_pairs<1>(g, q, f, P, buf, nfc_max, vp, nvp, blocks, out64, st);
 }
 
 }  // namespace gaca
