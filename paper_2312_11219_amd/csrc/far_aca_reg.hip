@@ -190,7 +190,8 @@ __global__ void __launch_bounds__(NT, MINW)
     // a row maximum above zt_hi is nonzero, one up to zt_lo zero; in between the root decides
     const double zt_hi = fmax(zero_tol * zero_tol * (1.0 + 1e-9), 1e-290);
     const double zt_lo = zero_tol * zero_tol * (1.0 - 1e-9);
-    const double mnd = (double)m * n * (1.0 + 1e-3);
+    // |u|^2 |w|^2 <= mnd max |u|^2: |w_j| <= 1 / (1 - tie), the pivot is that close to its row's maximum
+    const double mnd = (double)m * n / tie2 * (1.0 + 1e-3);
 
     FT rr[RX][CY];
 #pragma unroll
@@ -343,7 +344,7 @@ __global__ void __launch_bounds__(NT, MINW)
         ha = wave_umax(ha);
         ++q;
         if (nused >= m || q >= B.rho_max) break;
-        // max |u|^2 <= |u|^2 |w|^2 <= m n max |u|^2 (|w_j| <= 1 up to the tie, w_jp = 1)
+        // max |u|^2 <= |u|^2 |w|^2 <= mnd max |u|^2 (w_jp = 1)
         const double mlo = from_upper(ha), dlt = __builtin_amdgcn_sqrt(mnd * from_upper(ha + 1));
         s_hi += dlt;
         if (!(mlo > eps2 * (ref2 + s_hi * s_hi) * (1.0 + 1e-9))) {
