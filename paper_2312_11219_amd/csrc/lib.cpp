@@ -1859,6 +1859,7 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
             launch_far_map(bd, dact, nact, nlarge, s0);
             GACA_HIP_CHECK(hipEventRecord(ev[EV_F0], s0));
             launch_far_face(fk, p->g, p->f, bd, dact, nchunk, s0);
+            GACA_HIP_CHECK(hipGetLastError());
             GACA_HIP_CHECK(hipEventRecord(ev[EV_F1], s0));
             // work model of the face phase, while the face kernel runs
             for (int a = 0; a < nact; ++a) {
@@ -1881,8 +1882,13 @@ static void run_far(const std::vector<gaca_hmatrix *> &H, const double2 *dense,
             for (int k = 0; k < 4; ++k) cs[k] = multi ? ks[k] : s0;
             // this iteration's ACAs write the U, W slot that the previous iteration's copy
             // reads (on ks[0], in order before the class-0 launches there)
-            const bool copying = copy_ev && hipEventQuery(ev[EV_C]) != hipSuccess;
-            if (copying) (void)hipGetLastError();   // hipErrorNotReady
+            bool copying = false;
+            if (copy_ev) {
+                const hipError_t q = hipEventQuery(ev[EV_C]);
+                copying = q == hipErrorNotReady;
+                if (copying) (void)hipGetLastError();   // that is no error
+                else GACA_HIP_CHECK(q);
+            }
             for (int k = 0; k < 4; ++k) {
                 if (ccls[k] == 0) continue;
                 if (cs[k] != s0) GACA_HIP_CHECK(hipStreamWaitEvent(cs[k], ev[EV_F1], 0));
