@@ -422,14 +422,20 @@ __global__ void __launch_bounds__(256, 2)
 template <int WHAT, int KERNEL, int TIER, int G>
 void launch(const GeoDev &g, const QuadDev &q, const FreqDev &f, const NearSeries &S, const NearPair *pairs,
             int64_t npairs, const NearBlockDev *blocks, double2 *o64, float2 *o32, hipStream_t st) {
-    const dim3 nb((unsigned)((npairs * G + 255) / 256), S.nband);
+    // a grid holds fewer than 2^32 threads: G lanes a pair for at most 2^27 pairs
+    constexpr int64_t kPairs = (int64_t)1 << 27;
+    static_assert(kPairs * 16 < ((int64_t)1 << 32) && G <= 16, "threads of a launch");
+    for (; npairs > 0; pairs += kPairs, npairs -= kPairs) {
+        const int64_t n = npairs < kPairs ? npairs : kPairs;
+        const dim3 nb((unsigned)((n * G + 255) / 256), S.nband);
 #define GACA_SERIES(K) \
-    near_series_kernel<WHAT, KERNEL, TIER, K, G><<<nb, 256, 0, st>>>(g, q, f, S, pairs, npairs, blocks, o64, o32)
-    if (S.K == 16) GACA_SERIES(16);
-    else if (S.K == 20) GACA_SERIES(20);
-    else if (S.K == 24) GACA_SERIES(24);
-    else GACA_SERIES(30);
+    near_series_kernel<WHAT, KERNEL, TIER, K, G><<<nb, 256, 0, st>>>(g, q, f, S, pairs, n, blocks, o64, o32)
+        if (S.K == 16) GACA_SERIES(16);
+        else if (S.K == 20) GACA_SERIES(20);
+        else if (S.K == 24) GACA_SERIES(24);
+        else GACA_SERIES(30);
 #undef GACA_SERIES
+    }
 }
 
 }  // namespace
