@@ -447,7 +447,7 @@ __global__ void __launch_bounds__(512) apply_sum_rows_kernel(ApplyDev a, const X
                     const int steps = __builtin_amdgcn_readlane(q0_l, 63);
                     s_q1[wave][lane] = q0_l;
                     s_off[wave][lane] = off_l - (int64_t)(q0_l - rho_l) * m;
-                    __builtin_amdgcn_wave_barrier();
+                    wave_sync();
                     // step s of the block's sum: cross c with s_q1[c - 1] <= s < s_q1[c]
                     int c = 0;
                     for (int s0 = qs; s0 < steps; s0 += SU * QS) {
@@ -478,7 +478,7 @@ __global__ void __launch_bounds__(512) apply_sum_rows_kernel(ApplyDev a, const X
                             for (int v = 0; v < RC; ++v) acc[v] = cfma(uv[u], zv[u][v], acc[v]);
                     }
                     z += (int64_t)steps * nr;
-                    __builtin_amdgcn_wave_barrier();   // the next crosses take the same place
+                    wave_sync();   // the next crosses take the same place
                 }
             }
         }

@@ -114,6 +114,14 @@ __device__ __forceinline__ int wave_min(int v) {
                min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
+// LDS written by a wave's lanes before, read by others of the same wave after (the wave's accesses to LDS
+// keep their order; no instruction, but the compiler moves nothing across)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
 // Workgroup reductions; buf must hold >= 8 * NT / 64 doubles of shared memory.  Each call
 // writes the per-wave values into one of two slots (alternating from call to call), passes
 // one barrier and reads the slot back: a slot is written again only two calls later, after
