@@ -182,7 +182,7 @@ typedef struct {
                                      expand = U, W read + H_l written + the previous faces read
                                      for the Gram row; aca and tail 0 (not modelled) */
     /* aca phase by launch class (device time of the class's launches on its stream): faces held
-     * in registers with sides up to 32 (0), 33 to 96 (1), above 96 (2: up to 160 in FP64, 192
+     * in registers with sides up to 32 (0), 33 to 96 (1), above 96 (2: up to 128 in FP64, 192
      * mixed; together with the faces in HBM whose sides are <= 256 when threads_large is above
      * 256: 256 threads, two faces per CU); 3 the other faces (R in HBM, 512 threads by default) */
     double ms_far_by_kind[4];
@@ -195,7 +195,7 @@ typedef struct {
     int32_t launches_large_path[3];
     double far_flops_large_path[3];
     int32_t threads_large_used;   /* workgroup size of the class-3 launches */
-    int32_t threads_small_used;   /* workgroup size of the class-0 launches */
+    int32_t threads_small_used;   /* threads_small as given or tuned (without effect, see there) */
     int32_t autotune_state;       /* 0 sizes from the options, 1 chosen by timing each candidate
                                      during this problem's first build, 2 read from the
                                      autotune_cache file */

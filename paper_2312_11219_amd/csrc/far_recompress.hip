@@ -298,7 +298,7 @@ __global__ void __launch_bounds__(NT) far_recompress_small_kernel(AcaParams P, F
                                                                   int rlo) {
     using FT = rface_t<MIXED>;
     constexpr int LD = RM + 1;   // column stride: no power of two banks apart
-    constexpr int LP = 8;                 // lanes per pair (at most 16 pairs)
+    constexpr int LP = 8;                 // lanes per pair of columns (RM / 2 pairs)
     constexpr int HN = NT / 2;            // threads per factor
     static_assert(RM / 2 * LP <= NT && RM <= 64, "all pairs of a round at once, a lane per column");
     const int tid = threadIdx.x, half = (tid >> 6) & 1, hl = (tid & 63) + 64 * (tid >> 7);

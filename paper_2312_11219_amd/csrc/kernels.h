@@ -123,7 +123,7 @@ void launch_near_galerkin(int tier, const GeoDev &g, const QuadDev &q, const Fre
 // Far field 3D-ACA, run as iterations over all unfinished blocks of a batch; one iteration
 // adds one face (one 3-D cross, or one zero face) to every active block in four phases:
 //   face    residual face R = ENTRY(:, :, k) - sum_p coef_p H_p, all entries in parallel
-//   aca     partial-pivot ACA of R, one workgroup per block (R in registers up to sides of 160,
+//   aca     partial-pivot ACA of R, one workgroup per block (R in registers up to sides of 128,
 //           mixed 192; R in HBM above)
 //   expand  sides above 64: H_l = U W^T in 32 x 32 tiles with per-tile max, norm and Gram
 //           partials; up to 64 the ACA has stored H_l and found its pivot, and only the Gram row
@@ -180,9 +180,9 @@ void launch_far_map(const FarBatchDev &bd, const FarActive *act, int nact, int n
 void launch_far_face(int kernel, const GeoDev &g, const FreqDev &f, const FarBatchDev &bd,
                      const FarActive *act, int64_t nchunk, hipStream_t st);
 // Faces in registers (csrc/far_aca_reg.hip): class c takes both sides <= kFarRegSide[c]; the
-// mixed path all classes, FP64 all but the last two (160 x 160 double2 and the rest of a thread's
+// mixed path all classes, FP64 the first eight (160 x 160 double2 and the rest of a thread's
 // state exceed the registers of a CU).  Classes up to kFarEmitSide store H_l themselves.
-constexpr int kFarRegClasses = 10;
+constexpr int kFarRegClasses = 10, kFarRegClassesFp64 = 8;
 constexpr int kFarRegSide[kFarRegClasses] = {24, 32, 40, 48, 64, 80, 96, 128, 160, 192};
 constexpr int kFarEmitSide = 64;
 void launch_far_aca_reg(int cls, const AcaParams &P, const FarBatchDev &bd, const FarActive *act,

@@ -1279,7 +1279,7 @@ gaca_status gaca_problem_blocks(const gaca_problem *p, int64_t *far4, int64_t *n
 // Register class of a face in the aca phase (kFarRegSide), or -1 for the faces whose residual
 // stays in HBM: FP64 faces fit a CU's registers up to sides of 128, mixed ones up to 192.
 static int far_reg_class(int m, int n, bool mixed) {
-    const int side = std::max(m, n), ncls = mixed ? kFarRegClasses : kFarRegClasses - 2;
+    const int side = std::max(m, n), ncls = mixed ? kFarRegClasses : kFarRegClassesFp64;
     for (int c = 0; c < ncls; ++c)
         if (side <= kFarRegSide[c]) return c;
     return -1;
