@@ -26,8 +26,8 @@
 // rule has many points, the writes of the entries and the steps per frequency where it has few.  G lanes
 // share a pair and band, first its points, then its frequencies.  Near field of a build beside the far
 // field, every point at every frequency -> moments: Galerkin P0 (3072-triangle L-shape, L = 96) 82 -> 11 ms;
-// P1 double layer (4802-vertex sphere, L = 128) 49 -> 9.1 ms; collocation (9408-triangle sphere, L = 128)
-// 17.5 -> 10.8 ms, of which the writes of its 18 GB take 4.  (The power series took 6.2, 6.2 and 10.7.)
+// P1 double layer (4802-vertex sphere, L = 128) 49 -> 8.1 ms; collocation (9408-triangle sphere, L = 128)
+// 17.5 -> 10.8 ms, of which the writes of its 18 GB take 4.  (The power series took 6.1, 6.2 and 10.7.)
 // Pairs beyond the bound (few elements per wavelength) are left to the kernels that visit the points at
 // every frequency.
 #include <hip/hip_runtime.h>
@@ -81,7 +81,10 @@ struct Moments {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             m[k] = group_sum<G>(m[k]);
-            if (D) n[k] = group_sum<G>(n[k]);
+            if (D) {
+                n[k] = group_sum<G>(n[k]);
+                asm volatile("" : "+v"(m[k]), "+v"(n[k]));   // one after the other (registers)
+            }
         }
     }
     // sum_k a_k M_k (+ s sum_k a_k N_k), the terms at a[k step].  ONE: every lane of the wave takes this
@@ -99,7 +102,11 @@ struct Moments {
                 nr = fma(cr, n[k], nr);
                 ni = fma(ci, n[k], ni);
             }
-            if (ONE && k % 6 == 5) __builtin_amdgcn_sched_barrier(0);   // six terms in flight: more cost registers
+            // six terms in flight: more cost registers, of which the double layer has none left.  (The single
+            // layer runs with two waves per SIMD; with three it holds up the far field beside it: Galerkin
+            // 3072-triangle build 28.1 ms for 27.1.)
+            if (ONE && k % 6 == 5) __builtin_amdgcn_sched_barrier(0);
+            if (D && !ONE && k % 6 == 5) asm volatile("" : "+v"(pr), "+v"(pi), "+v"(nr), "+v"(ni) : : "memory");
         }
         if (D) {
             pr += sr * nr - si * ni;
