@@ -83,7 +83,8 @@ def write_traffic(fetch_db, write_db, copy_bytes, out_path):
             if COPY_KERNEL in name and copy is None:
                 copy = v
                 continue
-            short = re.sub(r"\(.*\)$", "", name).replace("void ", "").replace("gaca::", "")
+            short = name.replace("(anonymous namespace)::", "")
+            short = re.sub(r"\(.*\)$", "", short).replace("void ", "").replace("gaca::", "")
             if short.startswith("near_"):
                 starts.append(did)
             if not (short.startswith("far_") or short.startswith("near_")):

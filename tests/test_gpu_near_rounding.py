@@ -78,3 +78,30 @@ def test_rounding(scheme, kernel, Rrad):
     log(f"{scheme} {kernel} R rad {Rrad}: worst of the bar and error by class " +
         ", ".join(f"{t}: {a:.2f} {e:.1e}" for t, (a, e) in worst.items()))
     assert worst and max(a for a, _ in worst.values()) <= 1.0
+
+
+@pytest.mark.parametrize("scheme,kernel", [("collocation", "slp"), ("collocation", "dlp"), ("galerkin", "slp"),
+                                           ("p1", "dlp")])
+@pytest.mark.parametrize("left", [0.0, -6.0])
+def test_scattered_frequencies(scheme, kernel, left):
+    """Frequencies in no order, some twice, real ones, with real parts from `left` to 14: bands of one frequency
+    and of many.  Every near block against the entries point by point, 1e-13 of the block's largest at the
+    frequency (the bar of each side, (2 |s| r + 40) 2^-53, is below 2e-14 of the sum of the magnitudes)."""
+    import paper_2312_11219_amd as gaca
+    from inputs import lshape_mesh
+    rng = np.random.default_rng(8)
+    xyz, tri = lshape_mesh(3)
+    xyz = xyz + 0.02 * np.sin(17.0 * xyz + np.arange(3))
+    s = rng.uniform(left, 14.0, 27) + 1j * rng.uniform(-9.0, 9.0, 27)
+    s[5], s[11], s[12], s[20] = s[2], 14.0, left, s[3].real
+    prob = gaca.Problem(context(), xyz, tri, s, scheme=scheme, leaf_size=16, eps3d=1e-4, eps_aca=1e-6)
+    h, (_, near), perm = prob.build(kernel), prob.blocks(), prob.perm
+    worst = 0.0
+    for b in rng.permutation(len(near))[:40]:
+        r0, m, c0, n = (int(v) for v in near[b])
+        got = np.transpose(h.near_block(int(b), m, n), (0, 2, 1))
+        i, j, k = (v.ravel() for v in np.meshgrid(np.arange(m), np.arange(n), np.arange(len(s)), indexing="ij"))
+        ref = prob.eval_entries(kernel, perm[r0 + i], perm[c0 + j], k, np.zeros(i.size)).reshape(m, n, len(s))
+        worst = max(worst, (np.abs(got - ref).max((0, 1)) / np.maximum(np.abs(ref).max((0, 1)), 1e-300)).max())
+    log(f"{scheme} {kernel} real parts from {left}: largest difference {worst:.1e}")
+    assert worst <= 1e-13
