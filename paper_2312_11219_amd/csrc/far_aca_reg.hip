@@ -109,10 +109,12 @@ __device__ __forceinline__ double uniform(double x) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// x where the lane's bit of the wave-uniform mask is set, else 0
+// x where the lane's bit of the wave-uniform mask is set, else 0.  A mask that a vector instruction wrote (a
+// register restored from a lane, a comparison) may be read two wait states later; the compiler does not
+// look into the statement, so it brings them along.
 __device__ __forceinline__ unsigned keep(unsigned x, unsigned long long mask) {
     unsigned r;
-    asm("v_cndmask_b32_e64 %0, 0, %1, %2" : "=v"(r) : "v"(x), "s"(mask));
+    asm("s_nop 1\n\tv_cndmask_b32_e64 %0, 0, %1, %2" : "=v"(r) : "v"(x), "s"(mask));
     return r;
 }
 
