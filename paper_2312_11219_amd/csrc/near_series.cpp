@@ -107,7 +107,9 @@ void SeriesTables::build(double band_max, double reach, double rc_max, const dou
     if (!(S.half > 0.0) || !std::isfinite(S.half) || !std::isfinite(top)) return;
     S.nband = std::max(1, (int)std::ceil(0.5 * (hi - lo) * S.half / band_max));
     // A band costs its points' exponentials and sums, about two frequencies' worth of a point: with fewer than
-    // eight frequencies, or four a band, the points are visited at every frequency
+    // eight frequencies, or four a band, the points are visited at every frequency.  At four a band, near
+    // field of all pairs of 768 triangles, every point at every frequency -> moments: single layer 0.52 -> 0.29 ms
+    // (three bands), 0.69 -> 0.48 (five); Galerkin 9.7 -> 5.9, 13.7 -> 9.5; P1 2.3 -> 0.5, 3.4 -> 0.9
     if (n < 8 || n < 4 * S.nband || S.nband > kNearBands) return;
     rest = 1.001 * reach > S.half * (1.0 + 1e-12) || !(1.001 * rc_max <= S.rmax);
     std::vector<int> band(n, 0);
